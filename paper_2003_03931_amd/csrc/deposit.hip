@@ -406,114 +406,167 @@ __global__ __launch_bounds__(NT) void k_deposit_zm(Geom g, const int32_t* __rest
     }
 }
 
+// The value of the lane whose index differs in bit X (1 or 2), by DPP.
+template <int X>
+__device__ __forceinline__ unsigned quad_xor(unsigned v) {
+    constexpr int kPerm = X == 1 ? 0xB1 : 0x4E;      // quad_perm [1,0,3,2] or [2,3,0,1]
+    return (unsigned)__builtin_amdgcn_mov_dpp((int)v, kPerm, 0xf, 0xf, true);
+}
+
 // Coarse-mesh deposit (one mesh cell per storage cell): a workgroup owns a
 // BW^3 cube of mesh cells and walks the (BW+2)^3 storage cells that can reach
-// it, one cell per thread.  Along each axis a particle at in-cell byte m
-// weighs (in 1/512 of a cell) 255 - 2m and 2m + 257 on the cells at offsets
-// -1 and 0 when m < 128, and 767 - 2m and 2m - 255 on offsets 0 and +1
-// otherwise; the thread sums the 27 products over its cell's particles in
-// 32-bit registers (each product is below 2^27, so a sum of 24 is exact;
-// larger cells are summed 24 particles at a time) and adds each sum that
-// lands in the cube to a 64-bit LDS accumulator: one LDS atomic per cell and
-// slot instead of eight per particle, and no two lanes of an atomic on one
-// address.  The bytes of 8 particles are loaded together and the next cell's
-// range is fetched while the current cell is summed.  Integer sums: the
-// result does not depend on the order and equals the particle-by-particle
-// deposit bit for bit.
-template <int BW>
-__global__ __launch_bounds__(kDepThreads) void k_coarse_deposit(Geom g, const int32_t* __restrict__ offsets,
-                                                                 Planes p, float2* __restrict__ out, double scale) {
-    constexpr int SW = BW + 2;
+// it, one cell per lane (L = 1) or per quad of lanes (L = 4) at a time.  Along each axis a particle at in-cell
+// byte m weighs (in 1/512 of a cell) 255 - 2m and 2m + 257 on the cells at
+// offsets -1 and 0 when m < 128, and 767 - 2m and 2m - 255 on offsets 0 and
+// +1 otherwise.  The lane sums the 27 products over its cell's particles in
+// 32-bit registers, four particles at a time (one 4-byte load per axis, the
+// next four in flight meanwhile), and adds the sums to 64-bit LDS
+// accumulators that are padded by the slots' reach: no bounds checks,
+// constant offsets, one LDS atomic per cell and slot instead of eight per
+// particle.  A product is at most 511^3, so 32 of them fit 32 bits; fuller
+// cells are added every 32 particles.  A quad exchanges halves twice first,
+// so that each lane holds the whole sums of a quarter of the slots.  Integer
+// sums: the result does not depend on the order and equals the
+// particle-by-particle deposit bit for bit.
+//
+// Bound by vector instructions, about 60 per particle (HBM would take 1 ms of
+// a 1024^3 step's deposit).  A cell per thread with byte loads, bounds checks
+// per slot and a wave waiting at every cell for its fullest one took 9.06 ms
+// there, lanes stepping through their own cells take 5.68.
+template <int BW, int NT, int L>
+__global__ __launch_bounds__(NT) void k_coarse_deposit(Geom g, const int32_t* __restrict__ offsets, Planes p,
+                                                        float2* __restrict__ out, double scale) {
+    constexpr int SW = BW + 2, PW = BW + 4;
     constexpr int NS = SW * SW * SW;
-    constexpr int U = 8;                          // particles whose bytes are in flight together
-    constexpr int CH = 3 * U;                     // particles per exact 32-bit partial sum
-    __shared__ __align__(16) unsigned long long acc[BW * BW * BW];
+    constexpr int U = 4, ROUND = 32 / (U * L);    // particles together, and such loads per exact 32-bit sum
+    constexpr int CELLS = NT / L;                 // cells in work
+    static_assert(L == 1 || L == 4, "one lane or a quad");
+    __shared__ __align__(16) unsigned long long acc[PW * PW * PW];
+    __shared__ int s_axis[3][SW];                 // canonical index of a cell: one term per axis
     const int M = g.Nc;
     const int nbx = (M + BW - 1) / BW;
     const int b = (int)xcd_logical_block();
     const int T0[3] = {(b % nbx) * BW, ((b / nbx) % nbx) * BW, (b / (nbx * nbx)) * BW};
     const int bw[3] = {min(BW, M - T0[0]), min(BW, M - T0[1]), min(BW, M - T0[2])};
-    for (int i = threadIdx.x; i < BW * BW * BW / 2; i += kDepThreads)
+    static_assert(PW * PW * PW % 2 == 0, "accumulators are cleared 16 bytes at a time");
+    for (int i = threadIdx.x; i < PW * PW * PW / 2; i += NT)
         reinterpret_cast<uint4*>(acc)[i] = make_uint4(0u, 0u, 0u, 0u);
-    // particle range of window cell s (storage cell T0 - 1 + r); cells past a
-    // partial cube's reach are empty
-    auto range = [&](int s, int& st, int& en) {
-        const int rx = s % SW, ry = (s / SW) % SW, rz = s / (SW * SW);
+    if (threadIdx.x < 3 * SW) {
+        const int k = threadIdx.x / SW, r = threadIdx.x % SW;
+        const int c = wrapi(T0[k] - 1 + r, M);
+        s_axis[k][r] = (int)(k == 0 ? canon(g, c, 0, 0) : k == 1 ? canon(g, 0, c, 0) : canon(g, 0, 0, c));
+    }
+    __syncthreads();
+    // particle range of window cell s = r (storage cell T0 - 1 + r; empty past
+    // a partial cube's reach) and the padded cell of its first slot
+    auto range = [&](int s, int& st, int& en, int& at) {
+        const int row = s / SW, rz = s / (SW * SW), ry = row - rz * SW, rx = s - row * SW;
         st = en = 0;
+        at = s + 2 * row + 2 * PW * rz;
         if (s < NS && rx <= bw[0] + 1 && ry <= bw[1] + 1 && rz <= bw[2] + 1) {
-            const int64_t c = canon(g, wrapi(T0[0] - 1 + rx, M), wrapi(T0[1] - 1 + ry, M), wrapi(T0[2] - 1 + rz, M));
+            const int c = s_axis[0][rx] + s_axis[1][ry] + s_axis[2][rz];
             st = offsets[c];
             en = offsets[c + 1];
         }
     };
-    int nst, nen;
-    range(threadIdx.x, nst, nen);
-    __syncthreads();
-    for (int s = threadIdx.x; s < NS; s += kDepThreads) {
-        const int st = nst, en = nen;
-        range(s + kDepThreads, nst, nen);                         // next cell's range in flight
-        const int r[3] = {s % SW, (s / SW) % SW, s / (SW * SW)};
-        for (int q0 = st; q0 < en; q0 += CH) {
-            const int q1 = min(en, q0 + CH);
-            unsigned a[27];
+    // the planes are followed by others, so a load may pass the last
+    // particle by up to three bytes
+    auto load = [&](int q, unsigned mm[3]) {
 #pragma unroll
-            for (int k = 0; k < 27; ++k) a[k] = 0u;
-            for (int qb = q0; qb < q1; qb += U) {
-                unsigned mm[U][3];
+        for (int k = 0; k < 3; ++k) __builtin_memcpy(&mm[k], p.m[k] + q, U);
+    };
+    const int lane = L == 1 ? 0 : threadIdx.x % L;
+    int s = threadIdx.x / L, q, en, at, q_n, en_n, at_n;
+    range(s, q, en, at);
+    range(s + CELLS, q_n, en_n, at_n);
+    unsigned mm[3];
+    load(min(q + U * lane, (int)g.n), mm);
+    unsigned a[27];
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int q = min(qb + u, q1 - 1);
+    for (int k = 0; k < 27; ++k) a[k] = 0u;
+    int left = ROUND;
+    // every lane steps through its own cells: a wave is as long as the lane
+    // with the most particles, not the sum of each step's fullest cells
+    while (s < NS) {
+        const int q0 = q, e0 = en, at0 = at;
+        const bool done = q + U * L >= en;
+        q += U * L;
+        if (done) {
+            s += CELLS;
+            q = q_n;
+            en = en_n;
+            at = at_n;
+            range(s + CELLS, q_n, en_n, at_n);
+        }
+        unsigned mn[3];
+        load(min(q + U * lane, (int)g.n), mn);
 #pragma unroll
-                    for (int k = 0; k < 3; ++k) mm[u][k] = p.m[k][q];
-                }
+        for (int u = 0; u < U; ++u) {
+            unsigned w[3][3];
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const bool live = qb + u < q1;
-                    unsigned w[3][3];
+            for (int k = 0; k < 3; ++k) {
+                const unsigned m2 = 2u * ((mm[k] >> (8 * u)) & 255u);
+                w[k][0] = __builtin_elementwise_sub_sat(255u, m2);
+                w[k][2] = __builtin_elementwise_sub_sat(m2, 255u);
+                w[k][1] = 512u - (w[k][0] | w[k][2]);     // one of them is zero
+            }
+            const bool live = q0 + U * lane + u < e0;
 #pragma unroll
-                    for (int k = 0; k < 3; ++k) {
-                        const unsigned m = mm[u][k];
-                        const bool lo = m < 128u;
-                        w[k][0] = lo ? 255u - 2u * m : 0u;
-                        w[k][1] = lo ? 2u * m + 257u : 767u - 2u * m;
-                        w[k][2] = lo ? 0u : 2u * m - 255u;
-                    }
-                    if (!live) w[2][0] = w[2][1] = w[2][2] = 0u;
-                    unsigned wxy[9];
+            for (int k = 0; k < 3; ++k) w[2][k] = live ? w[2][k] : 0u;
+            unsigned wxy[9];
 #pragma unroll
-                    for (int j = 0; j < 3; ++j)
+            for (int j = 0; j < 3; ++j)
 #pragma unroll
-                        for (int i = 0; i < 3; ++i) wxy[3 * j + i] = (unsigned)__umul24(w[0][i], w[1][j]);
+                for (int i = 0; i < 3; ++i) wxy[3 * j + i] = (unsigned)__umul24(w[0][i], w[1][j]);
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+#pragma unroll
+                for (int j = 0; j < 9; ++j) a[9 * k + j] += (unsigned)__umul24(wxy[j], w[2][k]);
+        }
+        if (done || --left == 0) {
+            if (q0 < e0) {
+                // slot (i, j, k) is padded cell r + (i, j, k)
+                auto add = [&](int off, unsigned v) { atomicAdd(&acc[at0 + off], (unsigned long long)v); };
+                if constexpr (L == 1) {
 #pragma unroll
                     for (int k = 0; k < 3; ++k)
 #pragma unroll
-                        for (int j = 0; j < 9; ++j) a[9 * k + j] += (unsigned)__umul24(wxy[j], w[2][k]);
-                }
-            }
-            // slot (i, j, k) lands on cube cell r + (i, j, k) - 2
+                        for (int j = 0; j < 9; ++j) add((k * PW + j / 3) * PW + j % 3, a[9 * k + j]);
+                } else {
+                    // sum over the pair of lanes that differ in a bit: of x in
+                    // the lane whose bit is clear, of y in the other
+                    const bool b0 = lane & 1, b1 = lane & 2;
+                    auto half0 = [&](unsigned x, unsigned y) { return (b0 ? y : x) + quad_xor<1>(b0 ? x : y); };
+                    auto half1 = [&](unsigned x, unsigned y) { return (b1 ? y : x) + quad_xor<2>(b1 ? x : y); };
+                    unsigned h[14];           // slots 2t and 2t + 1 (the 28th is nothing)
 #pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                const int tz = r[2] + k - 2;
-                if (tz < 0 || tz >= bw[2]) continue;
+                    for (int t = 0; t < 14; ++t) h[t] = half0(a[2 * t], 2 * t + 1 < 27 ? a[2 * t + 1] : 0u);
 #pragma unroll
-                for (int j = 0; j < 3; ++j) {
-                    const int ty = r[1] + j - 2;
-                    if (ty < 0 || ty >= bw[1]) continue;
+                    for (int t = 0; t < 7; ++t) {
+                        // slots 4t .. 4t + 3 on lanes 0 .. 3
+                        const unsigned v = half1(h[2 * t], h[2 * t + 1]);
+                        int off[4];
 #pragma unroll
-                    for (int i = 0; i < 3; ++i) {
-                        const int tx = r[0] + i - 2;
-                        const unsigned v = a[9 * k + 3 * j + i];
-                        if (tx >= 0 && tx < bw[0] && v) atomicAdd(&acc[(tz * BW + ty) * BW + tx], (unsigned long long)v);
+                        for (int l = 0; l < 4; ++l) {
+                            const int m = 4 * t + l;
+                            off[l] = ((m / 9) * PW + m / 3 % 3) * PW + m % 3;
+                        }
+                        if (t < 6 || lane < 3) add(b1 ? (b0 ? off[3] : off[2]) : (b0 ? off[1] : off[0]), v);
                     }
                 }
             }
+#pragma unroll
+            for (int k = 0; k < 27; ++k) a[k] = 0u;
+            left = ROUND;
         }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) mm[k] = mn[k];
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < BW * BW * BW; i += kDepThreads) {
+    for (int i = threadIdx.x; i < BW * BW * BW; i += NT) {
         const int ix = i % BW, iy = (i / BW) % BW, iz = i / (BW * BW);
         if (ix >= bw[0] || iy >= bw[1] || iz >= bw[2]) continue;
-        const float v = (float)((double)acc[i] * scale - 1.0);
+        const float v = (float)((double)acc[((iz + 2) * PW + iy + 2) * PW + ix + 2] * scale - 1.0);
         out[(int64_t)(T0[0] + ix) + (int64_t)M * ((T0[1] + iy) + (int64_t)M * (T0[2] + iz))] = make_float2(v, 0.0f);
     }
 }
@@ -558,14 +611,32 @@ int ilog2(int v) {
 
 }  // namespace
 
+template <int BW, int NT, int L>
+void coarse_deposit_cubes(const Geom& g, const int32_t* offsets, Planes p, float2* mesh, double scale,
+                          hipStream_t s) {
+    const int nb = (g.Nc + BW - 1) / BW;
+    hipLaunchKernelGGL((k_coarse_deposit<BW, NT, L>), dim3(nb * nb * nb), dim3(NT), 0, s, g, offsets, p, mesh, scale);
+}
+
 void launch_coarse_deposit(const Geom& g, const int32_t* offsets, Planes p, float2* mesh, int32_t* /*overflow*/,
                            hipStream_t s) {
-    constexpr int BW = 16;
-    const int nb = (g.Nc + BW - 1) / BW;
     // acc in units of 2^-27 particle; density = mass / H^3 with H = r / f
     const double scale = std::ldexp(1.0, -27) * ((double)g.f * g.f * g.f) / ((double)g.r * g.r * g.r);
-    hipLaunchKernelGGL((k_coarse_deposit<BW>), dim3(nb * nb * nb), dim3(kDepThreads), 0, s, g, offsets, p, mesh,
-                       scale);
+    // Cubes of 16 cells re-read least (1.42x), but a small mesh has too few of
+    // them to fill the chip: at 64 cells a side 70 us against 35 with cubes of
+    // 8 (8 particles per cell), at 32 a side 60 against 13 with cubes of 4.
+    // Quads pay where a cell is a long walk (64 particles per cell: 590
+    // against 1592 us at 128 a side, a lane per cell also thrashing its cache
+    // lines) and cost nothing on small meshes; with 8 particles per cell on a
+    // large mesh most of a quad would idle (1.37 against 0.80 ms at 256).
+    if (g.Nc >= 128) {
+        if (g.r >= 4 * g.f) coarse_deposit_cubes<16, 512, 4>(g, offsets, p, mesh, scale, s);
+        else coarse_deposit_cubes<16, 512, 1>(g, offsets, p, mesh, scale, s);
+    } else if (g.Nc >= 64) {
+        coarse_deposit_cubes<8, 512, 4>(g, offsets, p, mesh, scale, s);
+    } else {
+        coarse_deposit_cubes<4, 256, 4>(g, offsets, p, mesh, scale, s);
+    }
 }
 
 void launch_fine_deposit(const Geom& g, const int32_t* offsets, Planes p, int tile0, int ntiles,
