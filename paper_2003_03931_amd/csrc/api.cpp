@@ -494,8 +494,8 @@ cube_status finish_general(cube_ctx* c, const StepPlan& next, void* scratch) {
     Planes src = c->B, dst = c->A;
     if (g.vcodec)
         for (int k = 0; k < 3; ++k) src.u[k] = dst.u[k] = nullptr;
-    launch_general_keys(g, c->offsets, c->dir, c->far_key, key, idx, s);
-    stable_sort_pairs(key, idx, kt, it, g.n, ilog2((int)std::min<int64_t>(g.ncells, 1 << 30)) + 1, ws, s);
+    launch_general_keys(g, c->offsets, c->dir, c->far_key, key, s);
+    stable_sort_pairs(key, idx, kt, it, g.n, ilog2((int)std::min<int64_t>(g.ncells, 1 << 30)) + 1, true, ws, s);
     launch_permute_planes(idx, src, dst, g.n, s);
     if (g.vcodec) launch_vc_encode(g, c->offsets_new, c->A, c->vcell, c->sc, c->partial, s, true);
     launch_commit_cells(c->counts_new, c->offsets_new, c->counts, c->offsets, g.ncells, c->sc, s);
@@ -778,36 +778,14 @@ cube_status cube_compress(cube_ctx* c, const float* pos, const float* vel, int64
     if (!tmp.get(&key, ub) || !tmp.get(&idx, ub) || !tmp.get(&kt, ub) || !tmp.get(&it, ub) || !tmp.get(&qp, ub) ||
         !tmp.get(&vmax, 256) || !tmp.get(&ws, sort_workspace_bytes(n)))
         return fail(CUBE_OOM, "compress: workspace allocation failed");
-    launch_encode_keys(g, dpos, key, qp, idx, n, s);
-    hipMemsetAsync(vmax, 0, sizeof(uint32_t), s);
-    launch_absmax_f32(dvel, 3 * n, vmax, s);
-    uint32_t vbits = 0;
-    hipMemcpyAsync(&vbits, vmax, sizeof(uint32_t), hipMemcpyDeviceToHost, s);
-    st = sync(c);
-    if (st != CUBE_OK) return st;
-    float vmaxf;
-    std::memcpy(&vmaxf, &vbits, sizeof(float));
-    double s0 = 1.0;
-    if (vmaxf > 0.0f) {
-        const double x = (double)c->desc.v_headroom * (double)vmaxf / 127.0;
-        int e;
-        const double m = std::frexp(x, &e);
-        s0 = (m == 0.5) ? std::ldexp(1.0, e - 1) : std::ldexp(1.0, e);
-    }
+    launch_encode_keys(g, dpos, dvel, key, qp, vmax, n, s);
+    launch_compress_scalars(c->sc, vmax, c->desc.v_headroom, s);
     int bits = ilog2((int)std::min<int64_t>(g.ncells, (int64_t)1 << 30));
     if (((int64_t)1 << bits) < g.ncells) ++bits;
-    if (bits < 1) bits = 1;
-    stable_sort_pairs(key, idx, kt, it, n, bits, ws, s);
-    launch_fill_i32(c->counts, 0, g.ncells + 16, s);
-    launch_count_keys(key, n, c->counts, s);
-    StepScalars init{};
-    init.s = s0;
-    init.s_next = s0;
-    *c->sc_host = init;
-    hipMemcpyAsync(c->sc, c->sc_host, sizeof(StepScalars), hipMemcpyHostToDevice, s);
-    exclusive_scan_i32(c->counts, c->offsets, g.ncells, c->scan_ws, s, &c->sc->max_count);
+    stable_sort_pairs(key, idx, kt, it, n, bits, true, ws, s);
+    launch_cell_offsets(key, n, g.ncells, c->counts, c->offsets, &c->sc->max_count, s);
     launch_max_block8(g, c->counts, &c->sc->max_block8, s);
-    launch_scatter_compressed(g, idx, qp, dvel, s0, c->A, c->counts, c->sc, n, s);
+    launch_scatter_compressed(idx, qp, dvel, c->A, c->sc, n, s);
     if (g.vcodec) launch_vc_encode(g, c->offsets, c->A, c->vcell, c->sc, c->partial, s);
     hipMemcpyAsync(c->sc_host, c->sc, sizeof(StepScalars), hipMemcpyDeviceToHost, s);
     st = sync(c);

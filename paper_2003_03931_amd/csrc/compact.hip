@@ -232,8 +232,7 @@ __global__ __launch_bounds__(kKThreads) void k_compact_brick(Geom g, const int32
 // keys of the general path: new canonical cell of every particle, old order
 __global__ __launch_bounds__(256) void k_general_keys(Geom g, const int32_t* __restrict__ offsets,
                                                        const uint8_t* __restrict__ dir,
-                                                       const uint32_t* __restrict__ far_key, uint32_t* __restrict__ key,
-                                                       uint32_t* __restrict__ idx) {
+                                                       const uint32_t* __restrict__ far_key, uint32_t* __restrict__ key) {
     extern __shared__ int offs[];
     const Chunk ch = chunk_of(g, blockIdx.x);
     for (int j = threadIdx.x; j <= g.Tc; j += blockDim.x) offs[j] = offsets[ch.c0 + j];
@@ -249,7 +248,6 @@ __global__ __launch_bounds__(256) void k_general_keys(Geom g, const int32_t* __r
             k = far_key[p];
         }
         key[p] = k;
-        idx[p] = (uint32_t)p;
     }
 }
 
@@ -286,10 +284,10 @@ void launch_compact_bricks(const Geom& g, const int32_t* offsets_old, const int3
 }
 
 void launch_general_keys(const Geom& g, const int32_t* offsets_old, const uint8_t* dir, const uint32_t* far_key,
-                         uint32_t* key, uint32_t* idx, hipStream_t s) {
+                         uint32_t* key, hipStream_t s) {
     const int64_t chunks = g.ncells / g.Tc;
     hipLaunchKernelGGL(k_general_keys, dim3((unsigned)chunks), dim3(256), (g.Tc + 1) * sizeof(int), s, g,
-                       offsets_old, dir, far_key, key, idx);
+                       offsets_old, dir, far_key, key);
 }
 
 void launch_permute_planes(const uint32_t* perm, Planes src, Planes dst, int64_t n, hipStream_t s) {

@@ -121,21 +121,26 @@ void exclusive_scan_i32(const int32_t* in, int32_t* out, int64_t n, void* ws, hi
 void launch_count_check(const int32_t* counts, int64_t n, long long* out, hipStream_t s);
 
 // ---- sort.hip -----------------------------------------------------------
-// Stable LSD sort of (key, value) pairs by the low `bits` key bits.
+// Stable LSD sort of (key, value) pairs by the low `bits` key bits; on return
+// key and val name the buffers that hold the result.  index_values: the
+// values are 0..n-1 and `val` need not be filled.
 size_t sort_workspace_bytes(int64_t n);
-void stable_sort_pairs(uint32_t* key, uint32_t* val, uint32_t* key_tmp, uint32_t* val_tmp,
-                       int64_t n, int bits, void* ws, hipStream_t s);
+void stable_sort_pairs(uint32_t*& key, uint32_t*& val, uint32_t*& key_tmp, uint32_t*& val_tmp, int64_t n, int bits,
+                       bool index_values, void* ws, hipStream_t s);
 
 // ---- codec.hip ----------------------------------------------------------
-void launch_encode_keys(const Geom& g, const float* pos, uint32_t* key, uint32_t* qpack,
-                        uint32_t* idx, int64_t n, hipStream_t s);
-void launch_absmax_f32(const float* v, int64_t n, uint32_t* out_bits, hipStream_t s);
-void launch_scatter_compressed(const Geom& g, const uint32_t* perm, const uint32_t* qpack,
-                               const float* vel, double s_v, Planes out, int32_t* counts,
-                               StepScalars* sc, int64_t n, hipStream_t st);
+// cell keys and packed in-cell bytes; *vmax = bits of the largest |vel|
+void launch_encode_keys(const Geom& g, const float* pos, const float* vel, uint32_t* key, uint32_t* qpack,
+                        uint32_t* vmax, int64_t n, hipStream_t s);
+// all scalars cleared but the velocity scale, which follows from *vmax
+void launch_compress_scalars(StepScalars* sc, const uint32_t* vmax, float headroom, hipStream_t s);
+// counts, offsets [ncells + 1] and atomicMax(*max_out, largest count) from sorted cell keys
+void launch_cell_offsets(const uint32_t* sorted_key, int64_t n, int64_t ncells, int32_t* counts, int32_t* offsets,
+                         int32_t* max_out, hipStream_t s);
+void launch_scatter_compressed(const uint32_t* perm, const uint32_t* qpack, const float* vel, Planes out,
+                               StepScalars* sc, int64_t n, hipStream_t s);
 void launch_decode(const Geom& g, const int32_t* offsets, Planes in, const StepScalars* sc,
                    const VelCells& vcell, float* pos, float* vel, hipStream_t s);
-void launch_count_keys(const uint32_t* key, int64_t n, int32_t* counts, hipStream_t s);
 
 // ---- vcodec.hip ---------------------------------------------------------
 // Cell-mean velocity codec (Eq. (3), Eq. (4)) on the FP32 velocities p.v of
@@ -251,7 +256,7 @@ void launch_compact_bricks(const Geom& g, const int32_t* offsets_old, const int3
                            const uint8_t* dir, const uint4* ment, const int32_t* mhdr, Planes src, Planes dst,
                            const StepScalars* sc, hipStream_t s);
 void launch_general_keys(const Geom& g, const int32_t* offsets_old, const uint8_t* dir,
-                         const uint32_t* far_key, uint32_t* key, uint32_t* idx, hipStream_t s);
+                         const uint32_t* far_key, uint32_t* key, hipStream_t s);
 void launch_permute_planes(const uint32_t* perm, Planes src, Planes dst, int64_t n, hipStream_t s);
 
 // ---- step.hip -----------------------------------------------------------
