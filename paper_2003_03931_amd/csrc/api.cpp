@@ -15,7 +15,6 @@
 // compaction moves B back into A in the new order.
 #include <algorithm>
 #include <chrono>
-#include <climits>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -384,10 +383,8 @@ void step_pre(cube_ctx* c) {
     const Geom& g = c->g;
     hipStream_t s = c->stream;
     StepScalars* sc = c->sc;
-    launch_step_prologue(sc, c->desc.v_headroom, s);
-    launch_fill_i32(c->counts_new, 0, g.ncells, s, &sc->halt);
     // the mover records of each tile go to the slots of its particles
-    launch_strided_copy(c->offsets, (int64_t)g.Tc * g.Tc * g.Tc, c->tcursor, g.ntiles, s, &sc->halt);
+    launch_step_begin(g, sc, c->desc.v_headroom, c->offsets, c->counts_new, c->tcursor, s);
     coarse_potential(c);
     pp_forces(c);
 }
@@ -415,15 +412,12 @@ void step_post(cube_ctx* c, const StepPlan& plan) {
     StepScalars* sc = c->sc;
     Profiler& P = c->prof;
     hipEvent_t es = P.on ? P.mark(s) : nullptr;
-    launch_fill_i32(&sc->new_max_count, 0, 2, s, &sc->halt);     // new_max_count and new_max_block8
-    exclusive_scan_i32(c->counts_new, c->offsets_new, g.ncells, c->scan_ws, s, &sc->new_max_count, &sc->halt);
-    launch_max_block8(g, c->counts_new, &sc->new_max_block8, s, &sc->halt);
-    if (P.on) P.add(ST_SCAN, es, P.mark(s), 8.0 * (double)g.ncells);
     if (c->dbg_force[2] > 0) {
         --c->dbg_force[2];
         launch_fill_i32(&sc->far_count, 1, 1, s, &sc->halt);
     }
-    launch_step_decide(sc, INT_MAX, s);
+    launch_step_scan(g, c->counts_new, c->offsets_new, c->scan_ws, sc, s);
+    if (P.on) P.add(ST_SCAN, es, P.mark(s), 8.0 * (double)g.ncells);
     // with the cell-mean codec the kicked FP32 velocities move instead of codes
     Planes src = c->B, dst = c->A;
     if (g.vcodec)
@@ -439,8 +433,7 @@ void step_post(cube_ctx* c, const StepPlan& plan) {
         // FP32 velocities read twice, codes written, cell means written
         if (P.on) P.add(ST_VENC, ev, P.mark(s), 27.0 * (double)g.n + 16.0 * (double)g.ncells);
     }
-    launch_commit_cells(c->counts_new, c->offsets_new, c->counts, c->offsets, g.ncells, sc, s);
-    launch_step_epilogue(sc, g, g.vcodec, plan.wide, plan.fmt == 2, s);
+    launch_step_commit(g, sc, c->counts_new, c->offsets_new, c->counts, c->offsets, plan.wide, plan.fmt == 2, s);
     if (c->dbg_force[3] > 0) {
         --c->dbg_force[3];
         launch_fill_i32(&sc->halt, 3, 1, s, &sc->halt);
@@ -498,8 +491,7 @@ cube_status finish_general(cube_ctx* c, const StepPlan& next, void* scratch) {
     stable_sort_pairs(key, idx, kt, it, g.n, ilog2((int)std::min<int64_t>(g.ncells, 1 << 30)) + 1, true, ws, s);
     launch_permute_planes(idx, src, dst, g.n, s);
     if (g.vcodec) launch_vc_encode(g, c->offsets_new, c->A, c->vcell, c->sc, c->partial, s, true);
-    launch_commit_cells(c->counts_new, c->offsets_new, c->counts, c->offsets, g.ncells, c->sc, s);
-    launch_step_epilogue(c->sc, g, g.vcodec, next.wide, next.fmt == 2, s);
+    launch_step_commit(g, c->sc, c->counts_new, c->offsets_new, c->counts, c->offsets, next.wide, next.fmt == 2, s);
     return launch_status(c);
 }
 
@@ -783,8 +775,8 @@ cube_status cube_compress(cube_ctx* c, const float* pos, const float* vel, int64
     int bits = ilog2((int)std::min<int64_t>(g.ncells, (int64_t)1 << 30));
     if (((int64_t)1 << bits) < g.ncells) ++bits;
     stable_sort_pairs(key, idx, kt, it, n, bits, true, ws, s);
-    launch_cell_offsets(key, n, g.ncells, c->counts, c->offsets, &c->sc->max_count, s);
-    launch_max_block8(g, c->counts, &c->sc->max_block8, s);
+    launch_key_offsets(key, n, g.ncells, c->counts, c->offsets, &c->sc->max_count, s);
+    launch_cell_stats(g, c->counts, &c->sc->max_block8, s);
     launch_scatter_compressed(idx, qp, dvel, c->A, c->sc, n, s);
     if (g.vcodec) launch_vc_encode(g, c->offsets, c->A, c->vcell, c->sc, c->partial, s);
     hipMemcpyAsync(c->sc_host, c->sc, sizeof(StepScalars), hipMemcpyDeviceToHost, s);
@@ -882,6 +874,51 @@ cube_status cube_forces(cube_ctx* c, float* acc, int32_t on_device) {
     return st;
 }
 
+namespace {
+
+// Copies that follow each other on both sides go as one (a view's planes are
+// mostly rows of one array, and so are the context's): a copy costs 2 to 4 us
+// whatever its size, and a state has seven arrays.
+struct CopyRuns {
+    hipStream_t stream;
+    hipMemcpyKind kind;
+    struct Part {
+        char* dst;
+        const char* src;
+        size_t bytes;
+    } part[12];
+    int parts = 0;
+
+    hipError_t copy(const Part& p, size_t bytes) { return hipMemcpyAsync(p.dst, p.src, bytes, kind, stream); }
+    hipError_t flush() {
+        size_t bytes = 0;
+        for (int i = 0; i < parts; ++i) bytes += part[i].bytes;
+        const int n = parts;
+        parts = 0;
+        if (n == 0 || copy(part[0], bytes) == hipSuccess) return hipSuccess;
+        // neighbours by chance: separate allocations are copied one by one
+        (void)hipGetLastError();
+        for (int i = 0; i < n; ++i) {
+            const hipError_t e = copy(part[i], part[i].bytes);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
+    hipError_t add(void* d, const void* s, size_t n) {
+        if (parts) {
+            const Part& last = part[parts - 1];
+            if (d != last.dst + last.bytes || s != last.src + last.bytes) {
+                const hipError_t e = flush();
+                if (e != hipSuccess) return e;
+            }
+        }
+        part[parts++] = {static_cast<char*>(d), static_cast<const char*>(s), n};
+        return hipSuccess;
+    }
+};
+
+}  // namespace
+
 cube_status cube_get_state(cube_ctx* c, cube_state_view* v) {
     cube_status st = check_ctx(c);
     if (st != CUBE_OK) return st;
@@ -889,15 +926,17 @@ cube_status cube_get_state(cube_ctx* c, cube_state_view* v) {
     if (!v || v->n_particles != g.n || v->n_cells != g.ncells) return fail(CUBE_INVALID, "state view size mismatch");
     hipStream_t s = c->stream;
     const hipMemcpyKind kind = v->on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-    for (int k = 0; k < 3; ++k) {
-        if (v->m[k]) CUBE_HIP(hipMemcpyAsync(v->m[k], c->A.m[k], g.n, kind, s));
-        if (v->u[k]) CUBE_HIP(hipMemcpyAsync(v->u[k], c->A.u[k], g.n, kind, s));
-    }
-    if (v->counts) CUBE_HIP(hipMemcpyAsync(v->counts, c->counts, g.ncells * sizeof(int32_t), kind, s));
-    if (v->ids && c->A.ids) CUBE_HIP(hipMemcpyAsync(v->ids, c->A.ids, g.n * sizeof(uint32_t), kind, s));
+    CopyRuns copy{s, kind, {}, 0};
+    for (int k = 0; k < 3; ++k)
+        if (v->m[k]) CUBE_HIP(copy.add(v->m[k], c->A.m[k], g.n));
+    for (int k = 0; k < 3; ++k)
+        if (v->u[k]) CUBE_HIP(copy.add(v->u[k], c->A.u[k], g.n));
+    if (v->counts) CUBE_HIP(copy.add(v->counts, c->counts, g.ncells * sizeof(int32_t)));
+    if (v->ids && c->A.ids) CUBE_HIP(copy.add(v->ids, c->A.ids, g.n * sizeof(uint32_t)));
     if (g.vcodec)
         for (int k = 0; k < 3; ++k)
-            if (v->vc[k]) CUBE_HIP(hipMemcpyAsync(v->vc[k], c->vcell.vc[k], g.ncells * sizeof(float), kind, s));
+            if (v->vc[k]) CUBE_HIP(copy.add(v->vc[k], c->vcell.vc[k], g.ncells * sizeof(float)));
+    CUBE_HIP(copy.flush());
     CUBE_HIP(hipMemcpyAsync(c->sc_host, c->sc, sizeof(StepScalars), hipMemcpyDeviceToHost, s));
     st = sync(c);
     if (st != CUBE_OK) return st;
@@ -920,18 +959,15 @@ cube_status cube_set_state(cube_ctx* c, const cube_state_view* v) {
     }
     hipStream_t s = c->stream;
     const hipMemcpyKind kind = v->on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
-    for (int k = 0; k < 3; ++k) {
-        CUBE_HIP(hipMemcpyAsync(c->A.m[k], v->m[k], g.n, kind, s));
-        CUBE_HIP(hipMemcpyAsync(c->A.u[k], v->u[k], g.n, kind, s));
-    }
-    CUBE_HIP(hipMemcpyAsync(c->counts, v->counts, g.ncells * sizeof(int32_t), kind, s));
+    CopyRuns copy{s, kind, {}, 0};
+    for (int k = 0; k < 3; ++k) CUBE_HIP(copy.add(c->A.m[k], v->m[k], g.n));
+    for (int k = 0; k < 3; ++k) CUBE_HIP(copy.add(c->A.u[k], v->u[k], g.n));
+    CUBE_HIP(copy.add(c->counts, v->counts, g.ncells * sizeof(int32_t)));
     if (g.vcodec)
-        for (int k = 0; k < 3; ++k)
-            CUBE_HIP(hipMemcpyAsync(c->vcell.vc[k], v->vc[k], g.ncells * sizeof(float), kind, s));
-    if (c->A.ids) {
-        if (v->ids) CUBE_HIP(hipMemcpyAsync(c->A.ids, v->ids, g.n * sizeof(uint32_t), kind, s));
-        else CUBE_HIP(hipMemsetAsync(c->A.ids, 0, g.n * sizeof(uint32_t), s));
-    }
+        for (int k = 0; k < 3; ++k) CUBE_HIP(copy.add(c->vcell.vc[k], v->vc[k], g.ncells * sizeof(float)));
+    if (c->A.ids && v->ids) CUBE_HIP(copy.add(c->A.ids, v->ids, g.n * sizeof(uint32_t)));
+    CUBE_HIP(copy.flush());
+    if (c->A.ids && !v->ids) CUBE_HIP(hipMemsetAsync(c->A.ids, 0, g.n * sizeof(uint32_t), s));
     StepScalars init{};
     init.s = v->s_v;
     init.s_next = v->s_v;
@@ -945,6 +981,9 @@ cube_status cube_set_state(cube_ctx* c, const cube_state_view* v) {
     CUBE_HIP(hipMemcpyAsync(dcheck, check, sizeof(check), hipMemcpyHostToDevice, s));
     launch_count_check(c->counts, g.ncells, dcheck, s);
     CUBE_HIP(hipMemcpyAsync(check, dcheck, sizeof(check), hipMemcpyDeviceToHost, s));
+    // (the offsets are only written here, read after the check)
+    launch_cell_offsets(g, c->counts, c->offsets, c->scan_ws, &c->sc->max_count, &c->sc->max_block8, s);
+    CUBE_HIP(hipMemcpyAsync(c->sc_host, c->sc, sizeof(StepScalars), hipMemcpyDeviceToHost, s));
     st = sync(c);
     if (st != CUBE_OK) return st;
     if (check[1] < 0 || check[0] != (long long)g.n) {
@@ -955,11 +994,6 @@ cube_status cube_set_state(cube_ctx* c, const cube_state_view* v) {
         sync(c);
         return fail(CUBE_INVALID, check[1] < 0 ? "negative cell count" : "counts do not sum to n_particles");
     }
-    exclusive_scan_i32(c->counts, c->offsets, g.ncells, c->scan_ws, s, &c->sc->max_count);
-    launch_max_block8(g, c->counts, &c->sc->max_block8, s);
-    CUBE_HIP(hipMemcpyAsync(c->sc_host, c->sc, sizeof(StepScalars), hipMemcpyDeviceToHost, s));
-    st = sync(c);
-    if (st != CUBE_OK) return st;
     c->max_count = c->sc_host->max_count;
     c->max_block8 = c->sc_host->max_block8;
     c->has_state = true;

@@ -120,7 +120,7 @@ __device__ __forceinline__ int lower_bound(const uint32_t* __restrict__ key, int
 // one by one took 396 us of atomics, this takes 30.)
 constexpr int kWalkKeys = 1 << 14;
 
-__global__ __launch_bounds__(256) void k_cell_offsets(const uint32_t* __restrict__ key, int64_t n, int64_t ncells,
+__global__ __launch_bounds__(256) void k_key_offsets(const uint32_t* __restrict__ key, int64_t n, int64_t ncells,
                                                       int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
                                                       int32_t* __restrict__ max_out) {
     __shared__ int below[2][256 / kWave];
@@ -346,9 +346,9 @@ void launch_compress_scalars(StepScalars* sc, const uint32_t* vmax, float headro
     hipLaunchKernelGGL(k_compress_scalars, dim3(1), dim3(256), 0, s, sc, vmax, (double)headroom);
 }
 
-void launch_cell_offsets(const uint32_t* sorted_key, int64_t n, int64_t ncells, int32_t* counts, int32_t* offsets,
-                         int32_t* max_out, hipStream_t s) {
-    hipLaunchKernelGGL(k_cell_offsets, dim3(grid1d(ncells, 256)), dim3(256), 0, s, sorted_key, n, ncells, counts,
+void launch_key_offsets(const uint32_t* sorted_key, int64_t n, int64_t ncells, int32_t* counts, int32_t* offsets,
+                        int32_t* max_out, hipStream_t s) {
+    hipLaunchKernelGGL(k_key_offsets, dim3(grid1d(ncells, 256)), dim3(256), 0, s, sorted_key, n, ncells, counts,
                        offsets, max_out);
 }
 

@@ -571,38 +571,6 @@ __global__ __launch_bounds__(NT) void k_coarse_deposit(Geom g, const int32_t* __
     }
 }
 
-// largest particle count of any 2 x 2 x 2 block of coarse cells (periodic).
-// Cells are visited in storage order (the +x, +y, +z neighbours are then
-// mostly 1, Tc and Tc^2 entries ahead); one atomic per workgroup.
-__global__ __launch_bounds__(256) void k_max_block8(Geom g, const int32_t* __restrict__ counts,
-                                                      int32_t* __restrict__ out, const int32_t* gate) {
-    if (gate && *(volatile const int32_t*)gate) return;
-    __shared__ int red[256 / kWave];
-    const int64_t tc3 = (int64_t)g.Tc * g.Tc * g.Tc;
-    int v = 0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < g.ncells;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t tile = i / tc3;
-        const int local = (int)(i - tile * tc3);
-        const int tx = (int)(tile % g.nt), ty = (int)((tile / g.nt) % g.nt), tz = (int)(tile / ((int64_t)g.nt * g.nt));
-        const int cx = tx * g.Tc + local % g.Tc, cy = ty * g.Tc + (local / g.Tc) % g.Tc;
-        const int cz = tz * g.Tc + local / (g.Tc * g.Tc);
-        const int x1 = cx + 1 == g.Nc ? 0 : cx + 1, y1 = cy + 1 == g.Nc ? 0 : cy + 1;
-        const int z1 = cz + 1 == g.Nc ? 0 : cz + 1;
-        const int sum = counts[i] + counts[canon(g, x1, cy, cz)] + counts[canon(g, cx, y1, cz)] +
-                        counts[canon(g, x1, y1, cz)] + counts[canon(g, cx, cy, z1)] + counts[canon(g, x1, cy, z1)] +
-                        counts[canon(g, cx, y1, z1)] + counts[canon(g, x1, y1, z1)];
-        v = max(v, sum);
-    }
-    v = wave_max(v);
-    if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = v;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < 256 / kWave; ++w) v = max(v, red[w]);
-        atomicMax(out, v);
-    }
-}
-
 int ilog2(int v) {
     int l = 0;
     while ((1 << l) < v) ++l;
@@ -681,12 +649,6 @@ bool fp16_density_fits(const Geom& g, int max_block8) {
     // a fine cell's density is at most f^3 times the particles of one 2 x 2 x 2
     // block of coarse cells; the plane transform's gain is divided out
     return (double)g.f * g.f * g.f * (double)max_block8 + 1.0 < 32768.0;
-}
-
-void launch_max_block8(const Geom& g, const int32_t* counts, int32_t* out, hipStream_t s, const int32_t* gate) {
-    const int64_t want = (g.ncells + 255) / 256;
-    hipLaunchKernelGGL(k_max_block8, dim3((unsigned)std::min<int64_t>(want, 4096)), dim3(256), 0, s, g, counts, out,
-                       gate);
 }
 
 void launch_diag_deposit(const Geom& g, const int32_t* offsets, Planes p, float2* mesh, hipStream_t s) {

@@ -60,8 +60,8 @@ __host__ __device__ inline int wrapi(int x, int n) {
 // A step's kernels that write the state or these scalars return at once
 // while `halt` is set; the host resolves a halt at its next synchronisation:
 //   1  the step needs the sorted general compaction (a particle moved more
-//      than one coarse cell, or a cell count exceeds the fast path's bound);
-//      everything up to the compaction is done and kept for it;
+//      than one coarse cell); everything up to the compaction is done and
+//      kept for it;
 //   2  a CUBE_MIXED_FP16 potential spectrum value left the FP16 range; the
 //      step is run again with FP32 spectra;
 //   3  the new state needs a wider fine-deposit accumulator or FP32 density
@@ -86,6 +86,7 @@ struct StepScalars {
     int32_t new_max_count;   // the same two of the step's new counts (set by the scan, adjacent)
     int32_t new_max_block8;
     int64_t steps_done;  // steps committed since the context was made
+    int32_t scan_ticket, commit_ticket;   // workgroups done in the step's scan and commit (cleared when it begins)
     // per-block maxima land in 64 slots (spreads atomic contention); the
     // epilogue folds them into max_u / max_carry
     int32_t umax_slot[64];
@@ -110,12 +111,23 @@ struct VelCells {
 };
 
 // ---- scan.hip -----------------------------------------------------------
-// out[0..n] = exclusive prefix sum of in[0..n-1]; out[n] = total.  If max_out
-// is given, atomicMax(max_out, max(in)) as well.
+// out[0..n] = exclusive prefix sum of in[0..n-1]; out[n] = total.
 size_t scan_workspace_bytes(int64_t n);
 // gate (optional): every kernel returns at once while *gate is nonzero.
 void exclusive_scan_i32(const int32_t* in, int32_t* out, int64_t n, void* ws, hipStream_t s,
-                        int32_t* max_out = nullptr, const int32_t* gate = nullptr);
+                        const int32_t* gate = nullptr);
+// atomicMax(*block8, largest count of a periodic 2 x 2 x 2 block of coarse cells)
+void launch_cell_stats(const Geom& g, const int32_t* counts, int32_t* block8, hipStream_t s);
+// offsets [ncells + 1] of the counts, and atomicMax of their largest and of
+// the largest block count; ws: scan_workspace_bytes(ncells)
+void launch_cell_offsets(const Geom& g, const int32_t* counts, int32_t* offsets, void* ws, int32_t* max_count,
+                         int32_t* block8, hipStream_t s);
+// the same for a step's new counts (into the scalars' new maxima), then the
+// step's decision: halt 2 on a spectrum overflow, else 1 when a particle moved
+// further than the fast compaction can take it.  Returns at once while
+// sc->halt is set.
+void launch_step_scan(const Geom& g, const int32_t* counts_new, int32_t* offsets_new, void* ws, StepScalars* sc,
+                      hipStream_t s);
 // out[0] += 64-bit sum of counts[0..n), out[1] = min(out[1], smallest count)
 // (out[0] = 0 and out[1] = INT64_MAX on entry)
 void launch_count_check(const int32_t* counts, int64_t n, long long* out, hipStream_t s);
@@ -135,8 +147,8 @@ void launch_encode_keys(const Geom& g, const float* pos, const float* vel, uint3
 // all scalars cleared but the velocity scale, which follows from *vmax
 void launch_compress_scalars(StepScalars* sc, const uint32_t* vmax, float headroom, hipStream_t s);
 // counts, offsets [ncells + 1] and atomicMax(*max_out, largest count) from sorted cell keys
-void launch_cell_offsets(const uint32_t* sorted_key, int64_t n, int64_t ncells, int32_t* counts, int32_t* offsets,
-                         int32_t* max_out, hipStream_t s);
+void launch_key_offsets(const uint32_t* sorted_key, int64_t n, int64_t ncells, int32_t* counts, int32_t* offsets,
+                        int32_t* max_out, hipStream_t s);
 void launch_scatter_compressed(const uint32_t* perm, const uint32_t* qpack, const float* vel, Planes out,
                                StepScalars* sc, int64_t n, hipStream_t s);
 void launch_decode(const Geom& g, const int32_t* offsets, Planes in, const StepScalars* sc,
@@ -161,9 +173,6 @@ void launch_fine_deposit(const Geom& g, const int32_t* offsets, Planes p, int ti
                          float* mesh, bool wide, hipStream_t s);
 bool fine_deposit_needs_wide(const Geom& g, int max_block8);
 bool fp16_density_fits(const Geom& g, int max_block8);
-// atomicMax(*out, largest count of a periodic 2 x 2 x 2 block of coarse cells)
-void launch_max_block8(const Geom& g, const int32_t* counts, int32_t* out, hipStream_t s,
-                       const int32_t* gate = nullptr);
 void launch_diag_deposit(const Geom& g, const int32_t* offsets, Planes p, float2* mesh,
                          hipStream_t s);
 
@@ -260,25 +269,20 @@ void launch_general_keys(const Geom& g, const int32_t* offsets_old, const uint8_
 void launch_permute_planes(const uint32_t* perm, Planes src, Planes dst, int64_t n, hipStream_t s);
 
 // ---- step.hip -----------------------------------------------------------
-// Prologue, decision, commit and epilogue of a step: all return at once while
-// sc->halt is set (the epilogue may set it, 3, after committing).
-void launch_step_prologue(StepScalars* sc, float v_headroom, hipStream_t s);
-// halt 2 on a spectrum overflow, else 1 when the fast compaction cannot run
-// (a far mover, or a cell count above fast_max_count in the old or new counts)
-void launch_step_decide(StepScalars* sc, int32_t fast_max_count, hipStream_t s);
-// counts <- counts_new, offsets <- offsets_new (ncells + 1 entries)
-void launch_commit_cells(const int32_t* counts_new, const int32_t* offsets_new, int32_t* counts, int32_t* offsets,
-                         int64_t ncells, const StepScalars* sc, hipStream_t s);
-// commit the scalars (s and max |u| only when vcodec == 0: the re-encode of
-// the cell-mean codec has set them); then halt 3 if the new state escapes the
-// plan of the next step (planned_wide: 64-bit fine-deposit accumulators;
-// planned_f16: FP16 density spectra)
-void launch_step_epilogue(StepScalars* sc, const Geom& g, int vcodec, bool planned_wide, bool planned_f16,
-                          hipStream_t s);
+// Begin and commit of a step: both return at once while sc->halt is set (the
+// commit may set it, 3, at its end).
+// Scalars for the coming kick, counts_new <- 0, and every tile's record cursor
+// at its first particle's index.
+void launch_step_begin(const Geom& g, StepScalars* sc, float v_headroom, const int32_t* offsets, int32_t* counts_new,
+                       int32_t* tcursor, hipStream_t s);
+// counts <- counts_new, offsets <- offsets_new (ncells + 1 entries); commit the
+// scalars (s and max |u| only when vcodec == 0: the re-encode of the cell-mean
+// codec has set them); then halt 3 if the new state escapes the plan of the
+// next step (planned_wide: 64-bit fine-deposit accumulators; planned_f16: FP16
+// density spectra)
+void launch_step_commit(const Geom& g, StepScalars* sc, const int32_t* counts_new, const int32_t* offsets_new,
+                        int32_t* counts, int32_t* offsets, bool planned_wide, bool planned_f16, hipStream_t s);
 void launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s, const int32_t* gate = nullptr);
-// out[i] = in[i * stride], i < n
-void launch_strided_copy(const int32_t* in, int64_t stride, int32_t* out, int64_t n, hipStream_t s,
-                         const int32_t* gate = nullptr);
 void launch_moments(const Geom& g, const int32_t* offsets, Planes p, const StepScalars* sc,
                     const VelCells& vcell, double* partial, int nblocks, hipStream_t s);
 void launch_reduce_partials(const double* partial, int nblocks, int width, double* out,

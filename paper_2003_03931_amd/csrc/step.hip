@@ -6,6 +6,7 @@
 // Diagnostics: momentum and kinetic energy of the decoded velocities summed in
 // FP64 in a fixed order (per-chunk partials, then one ordered reduction);
 // power-spectrum shells binned in FP64.
+#include <algorithm>
 #include <cmath>
 
 #include "common.h"
@@ -22,54 +23,45 @@ __device__ double pow2ceil_d(double x) {
 
 __device__ __forceinline__ bool halted(const StepScalars* sc) { return *(volatile const int32_t*)&sc->halt != 0; }
 
-__global__ void k_prologue(StepScalars* sc, float hv) {
-    if (threadIdx.x != 0 || halted(sc)) return;
+// Begin of a step: counters of the running step, the coming kick's scale, the
+// new counts cleared, the tiles' record cursors set.
+__global__ __launch_bounds__(256) void k_step_begin(StepScalars* sc, double hv, int4* __restrict__ counts_new,
+                                                    int64_t n4, const int32_t* __restrict__ offsets, int64_t tile_cells,
+                                                    int32_t* __restrict__ tcursor, int ntiles) {
+    if (halted(sc)) return;
+    const int64_t stride = (int64_t)gridDim.x * 256, first = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    for (int64_t i = first; i < n4; i += stride) counts_new[i] = make_int4(0, 0, 0, 0);
+    for (int64_t i = first; i < ntiles; i += stride) tcursor[i] = offsets[i * tile_cells];
+    if (blockIdx.x != 0) return;
+    if (threadIdx.x < 64) sc->umax_slot[threadIdx.x] = 0;
+    else if (threadIdx.x < 128) sc->cmax_slot[threadIdx.x - 64] = 0;
+    if (threadIdx.x != 0) return;
     const int M = sc->max_u;
     const double s = sc->s;
-    sc->s_next = (M == 0) ? s : pow2ceil_d(((double)hv * (double)M) * s / 127.0);
+    sc->s_next = (M == 0) ? s : pow2ceil_d((hv * (double)M) * s / 127.0);
     sc->max_u_next = 0;
     sc->far_count = 0;
     sc->max_carry = 0;
     sc->overflow = 0;
     sc->sat_step = 0;
-    for (int i = 0; i < 64; ++i) {
-        sc->umax_slot[i] = 0;
-        sc->cmax_slot[i] = 0;
-    }
+    sc->new_max_count = 0;
+    sc->new_max_block8 = 0;
+    sc->scan_ticket = 0;
+    sc->commit_ticket = 0;
 }
 
-__global__ void k_decide(StepScalars* sc, int32_t fast_max_count) {
-    if (threadIdx.x != 0 || halted(sc)) return;
-    if (sc->overflow) sc->halt = 2;
-    else if (sc->far_count > 0 || sc->max_count > fast_max_count || sc->new_max_count > fast_max_count) sc->halt = 1;
-}
+struct PlanCheck {
+    int vcodec, planned_wide, planned_f16;
+    double wide_cut, f16_cut, f3;
+};
 
-// counts <- counts_new and offsets <- offsets_new, 16 bytes at a time where aligned
-__global__ __launch_bounds__(256) void k_commit_cells(const int32_t* __restrict__ cn, const int32_t* __restrict__ on,
-                                                      int32_t* __restrict__ c, int32_t* __restrict__ o, int64_t ncells,
-                                                      const StepScalars* sc) {
-    if (halted(sc)) return;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t n4 = ncells / 4;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += stride) {
-        reinterpret_cast<int4*>(c)[i] = reinterpret_cast<const int4*>(cn)[i];
-        reinterpret_cast<int4*>(o)[i] = reinterpret_cast<const int4*>(on)[i];
-    }
-    for (int64_t i = 4 * n4 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i <= ncells; i += stride) {
-        if (i < ncells) c[i] = cn[i];
-        o[i] = on[i];
-    }
-}
-
-__global__ void k_epilogue(StepScalars* sc, int vcodec, int planned_wide, int planned_f16, double wide_cut,
-                           double f16_cut, double f3) {
-    if (threadIdx.x != 0 || halted(sc)) return;
+__device__ void epilogue(StepScalars* sc, const PlanCheck& pc) {
     int um = sc->max_u_next, cm = sc->max_carry;
     for (int i = 0; i < 64; ++i) {
         um = max(um, sc->umax_slot[i]);
         cm = max(cm, sc->cmax_slot[i]);
     }
-    if (!vcodec) {
+    if (!pc.vcodec) {
         sc->s = sc->s_next;
         sc->max_u = um;
     }
@@ -81,14 +73,33 @@ __global__ void k_epilogue(StepScalars* sc, int vcodec, int planned_wide, int pl
     sc->steps_done += 1;
     // the next step was enqueued for narrower accumulators or FP16 densities
     const double b8 = (double)sc->max_block8;
-    if ((!planned_wide && b8 >= wide_cut) || (planned_f16 && f3 * b8 + 1.0 >= f16_cut)) sc->halt = 3;
+    if ((!pc.planned_wide && b8 >= pc.wide_cut) || (pc.planned_f16 && pc.f3 * b8 + 1.0 >= pc.f16_cut)) sc->halt = 3;
 }
 
-__global__ void k_strided_copy(const int32_t* __restrict__ in, int64_t stride, int32_t* __restrict__ out, int64_t n,
-                               const int32_t* gate) {
-    if (gate && *(volatile const int32_t*)gate) return;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        out[i] = in[i * stride];
+__global__ void k_epilogue(StepScalars* sc, PlanCheck pc) {
+    if (threadIdx.x == 0 && !halted(sc)) epilogue(sc, pc);
+}
+
+// counts <- counts_new and offsets <- offsets_new, 16 bytes at a time where
+// aligned.  `last`: the last workgroup to finish commits the scalars; every
+// workgroup has then read the halt flag that this may set.
+__global__ __launch_bounds__(256) void k_commit_cells(const int32_t* __restrict__ cn, const int32_t* __restrict__ on,
+                                                      int32_t* __restrict__ c, int32_t* __restrict__ o, int64_t ncells,
+                                                      StepScalars* sc, int last, PlanCheck pc) {
+    if (halted(sc)) return;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    const int64_t n4 = ncells / 4;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += stride) {
+        reinterpret_cast<int4*>(c)[i] = reinterpret_cast<const int4*>(cn)[i];
+        reinterpret_cast<int4*>(o)[i] = reinterpret_cast<const int4*>(on)[i];
+    }
+    for (int64_t i = 4 * n4 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i <= ncells; i += stride) {
+        if (i < ncells) c[i] = cn[i];
+        o[i] = on[i];
+    }
+    if (!last) return;
+    __syncthreads();
+    if (threadIdx.x == 0 && atomicAdd(&sc->commit_ticket, 1) == (int)gridDim.x - 1) epilogue(sc, pc);
 }
 
 __global__ void k_fill(int32_t* p, int32_t v, int64_t n, const int32_t* gate) {
@@ -210,37 +221,28 @@ __global__ __launch_bounds__(256) void k_power_bins(const float2* __restrict__ d
 
 }  // namespace
 
-void launch_step_prologue(StepScalars* sc, float v_headroom, hipStream_t s) {
-    hipLaunchKernelGGL(k_prologue, dim3(1), dim3(64), 0, s, sc, v_headroom);
+void launch_step_begin(const Geom& g, StepScalars* sc, float v_headroom, const int32_t* offsets, int32_t* counts_new,
+                       int32_t* tcursor, hipStream_t s) {
+    // a side of the coarse mesh is a multiple of 4
+    const unsigned blocks = std::min(grid1d(g.ncells / 4, 256), 4096u);
+    hipLaunchKernelGGL(k_step_begin, dim3(blocks), dim3(256), 0, s, sc, (double)v_headroom,
+                       reinterpret_cast<int4*>(counts_new), g.ncells / 4, offsets, (int64_t)g.Tc * g.Tc * g.Tc, tcursor,
+                       g.ntiles);
 }
 
-void launch_step_decide(StepScalars* sc, int32_t fast_max_count, hipStream_t s) {
-    hipLaunchKernelGGL(k_decide, dim3(1), dim3(64), 0, s, sc, fast_max_count);
-}
-
-void launch_commit_cells(const int32_t* counts_new, const int32_t* offsets_new, int32_t* counts, int32_t* offsets,
-                         int64_t ncells, const StepScalars* sc, hipStream_t s) {
-    unsigned blocks = grid1d(ncells / 4 + 1, 256);
-    if (blocks > 8192) blocks = 8192;
-    hipLaunchKernelGGL(k_commit_cells, dim3(blocks), dim3(256), 0, s, counts_new, offsets_new, counts, offsets, ncells,
-                       sc);
-}
-
-void launch_step_epilogue(StepScalars* sc, const Geom& g, int vcodec, bool planned_wide, bool planned_f16,
-                          hipStream_t s) {
+void launch_step_commit(const Geom& g, StepScalars* sc, const int32_t* counts_new, const int32_t* offsets_new,
+                        int32_t* counts, int32_t* offsets, bool planned_wide, bool planned_f16, hipStream_t s) {
     // 32-bit fine accumulators hold D^3 units per particle of a 2x2x2 block of
     // coarse cells; FP16 density spectra hold f^3 per particle of such a block
-    const double wide_cut = std::ldexp(1.0, 32 - 3 * g.log2D);
-    const double f3 = (double)g.f * g.f * g.f;
-    hipLaunchKernelGGL(k_epilogue, dim3(1), dim3(64), 0, s, sc, vcodec, planned_wide ? 1 : 0, planned_f16 ? 1 : 0,
-                       wide_cut, 32768.0, f3);
-}
-
-void launch_strided_copy(const int32_t* in, int64_t stride, int32_t* out, int64_t n, hipStream_t s,
-                         const int32_t* gate) {
-    unsigned blocks = grid1d(n, 256);
-    if (blocks > 1024) blocks = 1024;
-    hipLaunchKernelGGL(k_strided_copy, dim3(blocks), dim3(256), 0, s, in, stride, out, n, gate);
+    const PlanCheck pc{g.vcodec, planned_wide ? 1 : 0, planned_f16 ? 1 : 0, std::ldexp(1.0, 32 - 3 * g.log2D), 32768.0,
+                       (double)g.f * g.f * g.f};
+    const unsigned blocks = std::min(grid1d(g.ncells / 4 + 1, 256), 8192u);
+    // the workgroups' atomics on one address take 12 ns each: above some
+    // hundreds of them a launch costs less
+    const bool last = blocks <= 256;
+    hipLaunchKernelGGL(k_commit_cells, dim3(blocks), dim3(256), 0, s, counts_new, offsets_new, counts, offsets,
+                       g.ncells, sc, last ? 1 : 0, pc);
+    if (!last) hipLaunchKernelGGL(k_epilogue, dim3(1), dim3(64), 0, s, sc, pc);
 }
 
 void launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s, const int32_t* gate) {
