@@ -238,7 +238,7 @@ Footprint footprint_of(const Geom& g, const cube_box_desc& d) {
     const int64_t t_green = r((int64_t)fine_green_workspace_bytes(g));
     const int64_t t_compress = 2 * r(12 * n) + 5 * r(4 * n) + r(256) + sortw;
     const int64_t t_general = 4 * r(4 * n) + sortw;
-    const int64_t t_pk = r(8 * n) + r(8 * (int64_t)g.ns) + r(8 * 3 * (int64_t)g.ns * std::max(1, g.ns / 4 - 1));
+    const int64_t t_pk = r(8 * n) + r(8 * (int64_t)g.ns) + r(8 * 3 * (int64_t)(g.ns + 1) * std::max(1, g.ns / 4 - 1));
     return {p, std::max(std::max(t_green, t_compress), std::max(t_general, t_pk))};
 }
 
@@ -1007,10 +1007,8 @@ cube_status cube_diagnostics(cube_ctx* c, cube_diag* out) {
     if (!out) return fail(CUBE_INVALID, "null output");
     const Geom& g = c->g;
     hipStream_t s = c->stream;
-    const int chunks = (int)(g.ncells / g.Tc);
     std::memset(out, 0, sizeof(*out));
-    launch_moments(g, c->offsets, c->A, c->sc, c->vcell, c->partial, chunks, s);
-    launch_reduce_partials(c->partial, chunks, 4, c->reduced, s);
+    launch_moments(g, c->offsets, c->A, c->sc, c->vcell, c->partial, c->reduced, s);
     double mom[4];
     CUBE_HIP(hipMemcpyAsync(mom, c->reduced, sizeof(mom), hipMemcpyDeviceToHost, s));
     int32_t total = 0;
@@ -1032,25 +1030,20 @@ cube_status cube_diagnostics(cube_ctx* c, cube_diag* out) {
     // potential energy: 1/2 sum over particles of phi_f + phi_c at their
     // positions (again with FP32 spectra if a FP16 one left its range)
     double wsum = 0.0;
-    std::vector<double> part;
     for (int attempt = 0; attempt < 2; ++attempt) {
         const StepPlan plan = plan_of(c, attempt > 0);
         launch_fill_i32(&c->sc->overflow, 0, 1, s);
         coarse_potential(c);
-        wsum = 0.0;
         for (int t0 = 0; t0 < g.ntiles; t0 += c->batch) {
             const int nt = std::min(c->batch, g.ntiles - t0);
             fine_potential(c, plan, t0, nt);
             GatherArgs a = gather_args(c, GATHER_POTENTIAL, t0, nt, c->step);
             a.partial = c->partial;
             launch_gather(a, s);
-            const int64_t np = (int64_t)gather_blocks_per_tile(g) * nt;
-            part.resize(np);
-            CUBE_HIP(hipMemcpyAsync(part.data(), c->partial, np * sizeof(double), hipMemcpyDeviceToHost, s));
-            st = sync(c);
-            if (st != CUBE_OK) return st;
-            for (double v : part) wsum += v;
+            // one running sum over the batches, in their order
+            launch_reduce_partials(c->partial, gather_blocks_per_tile(g) * nt, 1, c->reduced + 8, t0 > 0, s);
         }
+        CUBE_HIP(hipMemcpyAsync(&wsum, c->reduced + 8, sizeof(double), hipMemcpyDeviceToHost, s));
         int32_t oflow = 0;
         CUBE_HIP(hipMemcpyAsync(&oflow, &c->sc->overflow, sizeof(int32_t), hipMemcpyDeviceToHost, s));
         st = sync(c);
@@ -1076,23 +1069,20 @@ cube_status cube_power_spectrum(cube_ctx* c, int32_t nbins, double* k, double* p
     const int64_t cells = (int64_t)n * n * n;
     Temp tmp(c->mem);
     if (!tmp.get(&mesh, cells * sizeof(float2)) || !tmp.get(&tw, n * sizeof(float2)) ||
-        !tmp.get(&part, (size_t)n * 3 * nbins * sizeof(double)))
+        !tmp.get(&part, (size_t)(n + 1) * 3 * nbins * sizeof(double)))
         return fail(CUBE_OOM, "P(k) workspace");
-    fft_make_twiddles(n, tw, s);
-    launch_diag_deposit(g, c->offsets, c->A, mesh, s);
+    const std::vector<float2> tw_host = fft_twiddles(n);       // lives until the synchronisation below
+    hipMemcpyAsync(tw, tw_host.data(), n * sizeof(float2), hipMemcpyHostToDevice, s);
+    launch_diag_deposit(g, c->offsets, c->A, mesh, c->max_block8, s);
     fft3d(mesh, n, 1, false, tw, s);
-    launch_power_bins(mesh, n, nbins, part, n, s);
-    std::vector<double> h((size_t)n * 3 * nbins);
-    hipMemcpyAsync(h.data(), part, h.size() * sizeof(double), hipMemcpyDeviceToHost, s);
+    double* sums = part + (size_t)n * 3 * nbins;
+    launch_power_bins(mesh, n, nbins, part, sums, s);
+    std::vector<double> h((size_t)3 * nbins);
+    hipMemcpyAsync(h.data(), sums, h.size() * sizeof(double), hipMemcpyDeviceToHost, s);
     st = sync(c);
     if (st != CUBE_OK) return st;
     for (int j = 0; j < nbins; ++j) {
-        double ps = 0.0, ks = 0.0, cs = 0.0;
-        for (int z = 0; z < n; ++z) {
-            ps += h[(size_t)z * 3 * nbins + j];
-            ks += h[(size_t)z * 3 * nbins + nbins + j];
-            cs += h[(size_t)z * 3 * nbins + 2 * nbins + j];
-        }
+        const double ps = h[j], ks = h[nbins + j], cs = h[2 * nbins + j];
         nmodes[j] = (int64_t)llround(cs);
         pk[j] = cs > 0 ? ps / cs : 0.0;
         k[j] = cs > 0 ? ks / cs : 0.0;

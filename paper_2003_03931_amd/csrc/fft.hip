@@ -1072,13 +1072,18 @@ void fft_tiles_convolve(float* real_tiles, void* spec_tiles, int n, int ntiles, 
     tiles_for(n)(real_tiles, spec_tiles, ntiles, tw, green_octant, spec_format, range_flag, out_lo, out_hi, s, ev);
 }
 
-void fft_make_twiddles(int n, float2* dev_table, hipStream_t s) {
+std::vector<float2> fft_twiddles(int n) {
     std::vector<float2> h(n);
     for (int k = 0; k < n; ++k) {
         // exact argument reduction: angle = 2 pi k / n in FP64, one rounding to FP32
         const double ang = 2.0 * M_PI * (double)k / (double)n;
         h[k] = make_float2((float)std::cos(ang), (float)(-std::sin(ang)));
     }
+    return h;
+}
+
+void fft_make_twiddles(int n, float2* dev_table, hipStream_t s) {
+    const std::vector<float2> h = fft_twiddles(n);
     hipMemcpyAsync(dev_table, h.data(), n * sizeof(float2), hipMemcpyHostToDevice, s);
     hipStreamSynchronize(s);
 }

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <cstdint>
 #include <cstddef>
+#include <vector>
 
 namespace cube {
 
@@ -173,13 +174,16 @@ void launch_fine_deposit(const Geom& g, const int32_t* offsets, Planes p, int ti
                          float* mesh, bool wide, hipStream_t s);
 bool fine_deposit_needs_wide(const Geom& g, int max_block8);
 bool fp16_density_fits(const Geom& g, int max_block8);
-void launch_diag_deposit(const Geom& g, const int32_t* offsets, Planes p, float2* mesh,
+// rho - 1 on n_side^3 cells; max_block8 (the state's) decides the accumulators' width
+void launch_diag_deposit(const Geom& g, const int32_t* offsets, Planes p, float2* mesh, int max_block8,
                          hipStream_t s);
 
 // ---- fft.hip ------------------------------------------------------------
 bool fft_supported(int n);
 // Twiddle table exp(-2 pi i k / n), FP64-derived, n entries (device memory).
 void fft_make_twiddles(int n, float2* dev_table, hipStream_t s);
+// the same on the host, for a caller that copies it itself
+std::vector<float2> fft_twiddles(int n);
 // Forward or inverse 3-D transform of `batch` cubes of side n.
 void fft3d(float2* data, int n, int batch, bool inverse, const float2* tw, hipStream_t s);
 // Forward 3-D, multiply by a real octant Green's table, inverse 3-D.
@@ -283,11 +287,13 @@ void launch_step_begin(const Geom& g, StepScalars* sc, float v_headroom, const i
 void launch_step_commit(const Geom& g, StepScalars* sc, const int32_t* counts_new, const int32_t* offsets_new,
                         int32_t* counts, int32_t* offsets, bool planned_wide, bool planned_f16, hipStream_t s);
 void launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s, const int32_t* gate = nullptr);
+// FP64 sums of v_x, v_y, v_z, v^2 into out[0..3]; partial: at least 4 ncells / Tc doubles
 void launch_moments(const Geom& g, const int32_t* offsets, Planes p, const StepScalars* sc,
-                    const VelCells& vcell, double* partial, int nblocks, hipStream_t s);
-void launch_reduce_partials(const double* partial, int nblocks, int width, double* out,
-                            hipStream_t s);
-void launch_power_bins(const float2* dk, int n, int nbins, double* partial, int nparts,
-                       hipStream_t s);
+                    const VelCells& vcell, double* partial, double* out, hipStream_t s);
+// out[c] = (add ? out[c] : 0) + sum_b partial[b * width + c], fixed order
+void launch_reduce_partials(const double* partial, int nblocks, int width, double* out, bool add, hipStream_t s);
+// shell sums of |dk|^2 / n^3, of |k| and mode counts into out[3][nbins]
+// (partial: n planes of 3 nbins doubles)
+void launch_power_bins(const float2* dk, int n, int nbins, double* partial, double* out, hipStream_t s);
 
 }  // namespace cube

@@ -144,10 +144,52 @@ __global__ __launch_bounds__(256) void k_moments(Geom g, const int32_t* __restri
     }
 }
 
-// out[c] = sum_b partial[b * width + c], fixed order
-__global__ __launch_bounds__(256) void k_reduce_partials(const double* __restrict__ partial, int nblocks, int width,
-                                                         double* __restrict__ out) {
-    __shared__ double red[256 / kWave];
+// The same sums for linear codes v = u s: u and u^2 are summed as integers,
+// four codes per load, and scaled once per workgroup.  Every partial sum is an
+// integer (below 2^45) times a power of two, so the result is the exact one.
+constexpr int kMomentThreads = 256;
+
+__global__ __launch_bounds__(kMomentThreads) void k_moments_linear(Planes p, int64_t n4,
+                                                                   const StepScalars* __restrict__ sc,
+                                                                   double* __restrict__ partial) {
+    __shared__ long long red[4][kMomentThreads / kWave];
+    long long t[4] = {0, 0, 0, 0};
+    for (int64_t i = (int64_t)blockIdx.x * kMomentThreads + threadIdx.x; i < n4;
+         i += (int64_t)gridDim.x * kMomentThreads) {
+        int sq = 0;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const uint32_t w = reinterpret_cast<const uint32_t*>(p.u[k])[i];
+            int sum = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int u = (int)(int8_t)(w >> (8 * e));
+                sum += u;
+                sq += u * u;
+            }
+            t[k] += sum;
+        }
+        t[3] += sq;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+#pragma unroll
+        for (int d = kWave / 2; d > 0; d >>= 1) t[k] += __shfl_xor(t[k], d, kWave);
+        if ((threadIdx.x & (kWave - 1)) == 0) red[k][threadIdx.x / kWave] = t[k];
+    }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        long long v = 0;
+        for (int w = 0; w < kMomentThreads / kWave; ++w) v += red[threadIdx.x][w];
+        const double s = sc->s;
+        partial[(int64_t)blockIdx.x * 4 + threadIdx.x] = (double)v * (threadIdx.x < 3 ? s : s * s);
+    }
+}
+
+// out[c] (+)= sum_b partial[b * width + c], fixed order
+__global__ __launch_bounds__(1024) void k_reduce_partials(const double* __restrict__ partial, int nblocks, int width,
+                                                          double* __restrict__ out, int add) {
+    __shared__ double red[1024 / kWave];
     const int c = blockIdx.x;
     double acc = 0.0;
     for (int b = threadIdx.x; b < nblocks; b += blockDim.x) acc += partial[(int64_t)b * width + c];
@@ -157,7 +199,7 @@ __global__ __launch_bounds__(256) void k_reduce_partials(const double* __restric
     if (threadIdx.x == 0) {
         double t = 0.0;
         for (int w = 0; w < (int)(blockDim.x / kWave); ++w) t += red[w];
-        out[c] = t;
+        out[c] = add ? out[c] + t : t;
     }
 }
 
@@ -169,54 +211,74 @@ __device__ __forceinline__ long isqrt_floor(long v) {
     return q;
 }
 
-// One block per z-plane: shell sums of |dk|^2 / n^3, mode counts and |k|
-// sums.  A mode with integer |m|^2 = r2 falls in shell j = floor(sqrt(r2) +
-// 1/2) exactly when j^2 - j + 1 <= r2 <= j^2 + j, so each thread owns whole
-// shells and walks a shell's modes of the plane in a fixed order (rows m_y
-// ascending, then |m_x| ascending, + before -): the sums do not depend on
-// scheduling, and the spectrum is reproducible bit for bit.
-__global__ __launch_bounds__(256) void k_power_bins(const float2* __restrict__ dk, int n, int nbins,
-                                                    double* __restrict__ partial) {
-    const int z = blockIdx.x;
+// Shell sums of |dk|^2 / n^3, mode counts and |k| sums, a wave per z-plane and
+// shell.  A mode with integer |m|^2 = r2 falls in shell j = floor(sqrt(r2) +
+// 1/2) exactly when j^2 - j + 1 <= r2 <= j^2 + j, so a wave walks its shell's
+// modes of the plane: a row m_y per lane, |m_x| ascending, + before -, and
+// the lanes are added in a fixed order: the sums do not depend on scheduling,
+// and the spectrum is reproducible bit for bit.  (A thread per shell left most
+// of the chip idle: 355 us at 256^3, this takes 31.)
+constexpr int kBinWaves = 4;
+
+__global__ __launch_bounds__(kBinWaves* kWave) void k_power_bins(const float2* __restrict__ dk, int n, int nbins,
+                                                                 double* __restrict__ partial) {
+    const int z = blockIdx.y;
+    const int j = (int)blockIdx.x * kBinWaves + (int)threadIdx.x / kWave + 1;
+    if (j > nbins) return;
+    const int lane = threadIdx.x & (kWave - 1);
     const long mz = z <= n / 2 - 1 ? z : z - n;
     const int half = n / 2;
     const double inv_n3 = 1.0 / ((double)n * n * n);
     const double kf = 2.0 * M_PI / n;
-    for (int j = (int)threadIdx.x + 1; j <= nbins; j += blockDim.x) {
-        double ps = 0.0, ks = 0.0, cs = 0.0;
-        const long A0 = (long)j * j - j + 1 - mz * mz, B0 = (long)j * j + j - mz * mz;
-        if (B0 >= 0) {
-            const long ymax = isqrt_floor(B0);
-            for (long my = -ymax; my <= ymax; ++my) {
-                if (my < -half || my > half - 1) continue;
-                const long A = A0 - my * my, B = B0 - my * my;
-                if (B < 0) continue;
-                long lo = 0;
-                if (A > 0) {
-                    lo = isqrt_floor(A - 1) + 1;                        // ceil(sqrt(A))
-                }
-                const long hi = isqrt_floor(B);
-                const int y = (int)(my >= 0 ? my : my + n);
-                for (long mx = lo; mx <= hi; ++mx) {
-                    const double r = sqrt((double)(mx * mx + my * my + mz * mz));
+    double ps = 0.0, ks = 0.0, cs = 0.0;
+    const long A0 = (long)j * j - j + 1 - mz * mz, B0 = (long)j * j + j - mz * mz;
+    if (B0 >= 0) {
+        const long ymax = isqrt_floor(B0);
+        for (long my = -ymax + lane; my <= ymax; my += kWave) {
+            if (my < -half || my > half - 1) continue;
+            const long A = A0 - my * my, B = B0 - my * my;
+            if (B < 0) continue;
+            long lo = 0;
+            if (A > 0) {
+                lo = isqrt_floor(A - 1) + 1;                        // ceil(sqrt(A))
+            }
+            const long hi = isqrt_floor(B);
+            const int y = (int)(my >= 0 ? my : my + n);
+            for (long mx = lo; mx <= hi; ++mx) {
+                const double r = sqrt((double)(mx * mx + my * my + mz * mz));
 #pragma unroll
-                    for (int sgn = 0; sgn < 2; ++sgn) {
-                        if (sgn == 1 && mx == 0) break;
-                        const long sx = sgn ? -mx : mx;
-                        if (sx < -half || sx > half - 1) continue;
-                        const int x = (int)(sx >= 0 ? sx : sx + n);
-                        const float2 v = dk[((int64_t)z * n + y) * n + x];
-                        ps += ((double)v.x * v.x + (double)v.y * v.y) * inv_n3;
-                        ks += r * kf;
-                        cs += 1.0;
-                    }
+                for (int sgn = 0; sgn < 2; ++sgn) {
+                    if (sgn == 1 && mx == 0) break;
+                    const long sx = sgn ? -mx : mx;
+                    if (sx < -half || sx > half - 1) continue;
+                    const int x = (int)(sx >= 0 ? sx : sx + n);
+                    const float2 v = dk[((int64_t)z * n + y) * n + x];
+                    ps += ((double)v.x * v.x + (double)v.y * v.y) * inv_n3;
+                    ks += r * kf;
+                    cs += 1.0;
                 }
             }
         }
+    }
+    ps = wave_sum_d(ps);
+    ks = wave_sum_d(ks);
+    cs = wave_sum_d(cs);
+    if (lane == 0) {
         partial[(int64_t)z * 3 * nbins + (j - 1)] = ps;
         partial[(int64_t)z * 3 * nbins + nbins + (j - 1)] = ks;
         partial[(int64_t)z * 3 * nbins + 2 * nbins + (j - 1)] = cs;
     }
+}
+
+// out[i] = sum over z of partial[z][i], a wave per i, fixed order
+__global__ __launch_bounds__(kBinWaves* kWave) void k_sum_planes(const double* __restrict__ partial, int n, int width,
+                                                                 double* __restrict__ out) {
+    const int i = (int)blockIdx.x * kBinWaves + (int)threadIdx.x / kWave;
+    if (i >= width) return;
+    double t = 0.0;
+    for (int z = threadIdx.x & (kWave - 1); z < n; z += kWave) t += partial[(int64_t)z * width + i];
+    t = wave_sum_d(t);
+    if ((threadIdx.x & (kWave - 1)) == 0) out[i] = t;
 }
 
 }  // namespace
@@ -252,17 +314,29 @@ void launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s, const int3
 }
 
 void launch_moments(const Geom& g, const int32_t* offsets, Planes p, const StepScalars* sc,
-                    const VelCells& vcell, double* partial, int nblocks, hipStream_t s) {
-    hipLaunchKernelGGL(k_moments, dim3(nblocks), dim3(256), (g.Tc + 1) * sizeof(int), s, g, offsets, p, sc, vcell,
-                       partial);
+                    const VelCells& vcell, double* partial, double* out, hipStream_t s) {
+    int blocks = (int)(g.ncells / g.Tc);
+    if (g.vcodec) {
+        hipLaunchKernelGGL(k_moments, dim3(blocks), dim3(256), (g.Tc + 1) * sizeof(int), s, g, offsets, p, sc, vcell,
+                           partial);
+    } else {
+        // (the number of particles is a multiple of 64)
+        blocks = (int)std::min<int64_t>(std::min(blocks, 1024), (int64_t)grid1d(g.n / 4, kMomentThreads));
+        hipLaunchKernelGGL(k_moments_linear, dim3(blocks), dim3(kMomentThreads), 0, s, p, g.n / 4, sc, partial);
+    }
+    launch_reduce_partials(partial, blocks, 4, out, false, s);
 }
 
-void launch_reduce_partials(const double* partial, int nblocks, int width, double* out, hipStream_t s) {
-    hipLaunchKernelGGL(k_reduce_partials, dim3(width), dim3(256), 0, s, partial, nblocks, width, out);
+void launch_reduce_partials(const double* partial, int nblocks, int width, double* out, bool add, hipStream_t s) {
+    hipLaunchKernelGGL(k_reduce_partials, dim3(width), dim3(1024), 0, s, partial, nblocks, width, out, add ? 1 : 0);
 }
 
-void launch_power_bins(const float2* dk, int n, int nbins, double* partial, int /*nparts*/, hipStream_t s) {
-    hipLaunchKernelGGL(k_power_bins, dim3(n), dim3(256), 0, s, dk, n, nbins, partial);
+void launch_power_bins(const float2* dk, int n, int nbins, double* partial, double* out, hipStream_t s) {
+    const int width = 3 * nbins;
+    hipLaunchKernelGGL(k_power_bins, dim3((nbins + kBinWaves - 1) / kBinWaves, n), dim3(kBinWaves * kWave), 0, s, dk, n,
+                       nbins, partial);
+    hipLaunchKernelGGL(k_sum_planes, dim3((width + kBinWaves - 1) / kBinWaves), dim3(kBinWaves * kWave), 0, s, partial,
+                       n, width, out);
 }
 
 }  // namespace cube
