@@ -278,7 +278,7 @@ void coarse_potential(cube_ctx* c) {
     hipEvent_t e0 = P.on ? P.mark(c->stream) : nullptr;
     launch_coarse_deposit(g, c->offsets, c->A, c->coarse, nullptr, c->stream);
     hipEvent_t e1 = P.on ? P.mark(c->stream) : nullptr;
-    fft3d_convolve(c->coarse, g.Nc, 1, c->tw_coarse, c->coarse_green, 1, c->stream);
+    fft3d_convolve(c->coarse, g.Nc, 1, c->tw_coarse, c->coarse_green, c->stream);
     if (P.on) {
         hipEvent_t e2 = P.mark(c->stream);
         // deposit: complex mesh write + offsets read + 3 position bytes per particle
@@ -850,7 +850,7 @@ cube_status cube_forces(cube_ctx* c, float* acc, int32_t on_device) {
     // a FP16 potential spectrum out of range: evaluate again with FP32 spectra
     for (int attempt = 0; attempt < 2; ++attempt) {
         const StepPlan plan = plan_of(c, attempt > 0);
-        launch_fill_i32(&c->sc->overflow, 0, 1, s);
+        if (plan.fmt == 2) launch_fill_i32(&c->sc->overflow, 0, 1, s);
         coarse_potential(c);
         pp_forces(c);
         for (int t0 = 0; t0 < g.ntiles; t0 += c->batch) {
@@ -860,12 +860,13 @@ cube_status cube_forces(cube_ctx* c, float* acc, int32_t on_device) {
             a.acc = dacc;
             launch_gather(a, s);
         }
+        // (only FP16 spectra can leave their range)
         int32_t oflow = 0;
-        CUBE_HIP(hipMemcpyAsync(&oflow, &c->sc->overflow, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+        if (plan.fmt == 2)
+            CUBE_HIP(hipMemcpyAsync(&oflow, &c->sc->overflow, sizeof(int32_t), hipMemcpyDeviceToHost, s));
         st = sync(c);
         if (st != CUBE_OK) return st;
         if (!oflow) break;
-        if (attempt > 0) return fail(CUBE_OVERFLOW, "FP32 spectra raised the FP16 range flag");
     }
     if (!on_device) {
         CUBE_HIP(hipMemcpyAsync(acc, dacc, bytes, hipMemcpyDeviceToHost, s));
@@ -1032,7 +1033,7 @@ cube_status cube_diagnostics(cube_ctx* c, cube_diag* out) {
     double wsum = 0.0;
     for (int attempt = 0; attempt < 2; ++attempt) {
         const StepPlan plan = plan_of(c, attempt > 0);
-        launch_fill_i32(&c->sc->overflow, 0, 1, s);
+        if (plan.fmt == 2) launch_fill_i32(&c->sc->overflow, 0, 1, s);
         coarse_potential(c);
         for (int t0 = 0; t0 < g.ntiles; t0 += c->batch) {
             const int nt = std::min(c->batch, g.ntiles - t0);
@@ -1045,11 +1046,11 @@ cube_status cube_diagnostics(cube_ctx* c, cube_diag* out) {
         }
         CUBE_HIP(hipMemcpyAsync(&wsum, c->reduced + 8, sizeof(double), hipMemcpyDeviceToHost, s));
         int32_t oflow = 0;
-        CUBE_HIP(hipMemcpyAsync(&oflow, &c->sc->overflow, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+        if (plan.fmt == 2)
+            CUBE_HIP(hipMemcpyAsync(&oflow, &c->sc->overflow, sizeof(int32_t), hipMemcpyDeviceToHost, s));
         st = sync(c);
         if (st != CUBE_OK) return st;
         if (!oflow) break;
-        if (attempt > 0) return fail(CUBE_OVERFLOW, "FP32 spectra raised the FP16 range flag");
     }
     out->potential = 0.5 * wsum;
     return CUBE_OK;

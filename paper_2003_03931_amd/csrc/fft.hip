@@ -9,12 +9,14 @@
 // exp(-2 pi i k / N) computed in FP64 and rounded once to FP32.  The z pass
 // can fuse forward transform, multiplication by a real even Green's table
 // (stored as one octant) and inverse transform, so a Poisson solve is five
-// sweeps over the mesh: x, y, z+G+z^-1, y^-1, x^-1.
+// sweeps over the mesh: x, y, z+G+z^-1, y^-1, x^-1 -- three up to 112 points a
+// side, where an xy plane fits LDS.
 //
 // Conventions: forward uses exp(-2 pi i jk/N) like numpy; inverse is
 // unnormalised (the 1/N^3 is folded into the Green's tables).
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 #include <vector>
 
 #include "common.h"
@@ -338,11 +340,11 @@ constexpr int pencils() { return N <= 256 ? 16 : 8; }
 __device__ __forceinline__ int fold(int k, int n) { return k <= n / 2 ? k : n - k; }
 
 // KIND: 0 = x pencils, 1 = y pencils, 2 = z pencils.
-// MODE: 0 forward, 1 inverse, 2 forward * float table * inverse, 3 same with a double table.
+// MODE: 0 forward, 1 inverse, 2 forward * table * inverse.
 template <int N, int KIND, int MODE>
 __global__ __launch_bounds__(kFftThreads) void k_fft(float2* __restrict__ data, const float2* __restrict__ tw,
-                                                      const void* __restrict__ green) {
-    constexpr int W = pencils<N>();
+                                                      const double* __restrict__ green) {
+    constexpr int W = pencils<N>(), NT = kFftThreads;
     constexpr int LDN = N + 1;
     __shared__ float2 lds[W * LDN];
     float2* cube_base = data + (int64_t)blockIdx.y * N * N * N;
@@ -367,7 +369,7 @@ __global__ __launch_bounds__(kFftThreads) void k_fft(float2* __restrict__ data, 
         }
     }
     float2* g = cube_base + base;
-    stage_to_lds<kFftThreads, 8>(
+    stage_to_lds<NT, 8>(
         W * N, g, lds,
         [&](int e) {
             const int i = KIND == 0 ? e % N : e / W, w = KIND == 0 ? e / N : e % W;
@@ -377,38 +379,68 @@ __global__ __launch_bounds__(kFftThreads) void k_fft(float2* __restrict__ data, 
             const int i = KIND == 0 ? e % N : e / W, w = KIND == 0 ? e / N : e % W;
             return w * LDN + i;
         });
+    // G(kx, ky, kz): this block holds kz = i, ky = yz, kx = x0 + w.  Its loads
+    // are in flight during the forward transform (97 -> 82 us at 256^3, 1.32 ->
+    // 1.13 ms at 512^3, where every access of a pencil is in a page of its own).
+    constexpr int M = N / 2 + 1, UG = (W * N + NT - 1) / NT;
+    double gv[MODE == 2 ? UG : 1];
+    if (MODE == 2) {
+        const int fy = fold(yz, N);
+#pragma unroll
+        for (int u = 0; u < UG; ++u) {
+            const int e = u * NT + (int)threadIdx.x;
+            const int w = e % W, i = e / W;
+            if (e < W * N) gv[u] = green[((int64_t)fold(i, N) * M + fy) * M + fold(x0 + w, N)];
+        }
+        asm volatile("" ::: "memory");
+    }
     lds_barrier();
-    using L = Lay<W, 1, LDN, false, kFftThreads>;
+    using L = Lay<W, 1, LDN, false, NT>;
     if (MODE == 1) {
         Plan<N>::template run<L, true>(lds, tw);
     } else {
         Plan<N>::template run<L, false>(lds, tw);
     }
-    if (MODE >= 2) {
-        // multiply by G(kx, ky, kz): this block holds kz = i, ky = yz, kx = x0 + w
-        constexpr int M = N / 2 + 1;
-        const int fy = fold(yz, N);
-        for (int e = threadIdx.x; e < W * N; e += kFftThreads) {
-            const int w = e % W, i = e / W;
-            const int64_t gi = ((int64_t)fold(i, N) * M + fy) * M + fold(x0 + w, N);
-            float2 v = lds[w * LDN + i];
-            if (MODE == 2) {
-                const float gv = static_cast<const float*>(green)[gi];
-                v = make_float2(v.x * gv, v.y * gv);
-            } else {
-                const double gv = static_cast<const double*>(green)[gi];
-                v = make_float2((float)((double)v.x * gv), (float)((double)v.y * gv));
+    if (MODE == 2) {
+#pragma unroll
+        for (int u = 0; u < UG; ++u) {
+            const int e = u * NT + (int)threadIdx.x;
+            if (e < W * N) {
+                float2& v = lds[(e % W) * LDN + e / W];
+                v = make_float2((float)((double)v.x * gv[u]), (float)((double)v.y * gv[u]));
             }
-            lds[w * LDN + i] = v;
         }
         lds_barrier();
         Plan<N>::template run<L, true>(lds, tw);
     }
-    for (int e = threadIdx.x; e < W * N; e += kFftThreads) {
+    for (int e = threadIdx.x; e < W * N; e += NT) {
         int i, w;
         if (KIND == 0) { i = e % N; w = e / N; } else { w = e % W; i = e / W; }
         g[i * stride_i + w * stride_w] = lds[w * LDN + i];
     }
+}
+
+// Both transforms of an xy plane of a small cube (x then y, or y then x), the
+// plane in LDS: one sweep over the mesh and one launch instead of two.  The
+// one-dimensional transforms are those of k_fft, value by value (at 128 points
+// the compiler fuses another of a twiddle's products, so 128 keeps its passes).
+constexpr int kPlaneMax = 112;                 // 101 KB of LDS
+template <int N>
+constexpr int xy_threads() { return N * N / 8 >= 1024 ? 1024 : (N * N / 8 + 63) / 64 * 64; }
+
+template <int N, bool INV, bool Y_FIRST>
+__global__ __launch_bounds__(xy_threads<N>()) void k_fft_xy(float2* __restrict__ data, const float2* __restrict__ tw) {
+    constexpr int NT = xy_threads<N>(), LDN = N + 1;
+    __shared__ float2 lds[N * LDN];
+    float2* g = data + ((int64_t)blockIdx.y * N + blockIdx.x) * N * N;
+    stage_to_lds<NT, 8>(
+        N * N, g, lds, [&](int e) { return e; }, [&](int e) { return (e / N) * LDN + e % N; });
+    lds_barrier();
+    using X = Lay<N, 1, LDN, false, NT>;
+    using Y = Lay<N, LDN, 1, true, NT>;
+    Plan<N>::template run<typename std::conditional<Y_FIRST, Y, X>::type, INV>(lds, tw);
+    Plan<N>::template run<typename std::conditional<Y_FIRST, X, Y>::type, INV>(lds, tw);
+    for (int e = threadIdx.x; e < N * N; e += NT) g[e] = lds[(e / N) * LDN + e % N];
 }
 
 // ---- storage of the half spectra between the tile sweeps ----------------
@@ -1015,54 +1047,58 @@ TilesFn tiles_for(int n) {
     }
 }
 
+// One or two sweeps over `batch` cubes: the transforms of the xy planes in
+// either order, or a z pass (which also convolves).
+enum Sweep { SWEEP_XY, SWEEP_XY_INV, SWEEP_YX_INV, SWEEP_Z, SWEEP_Z_INV, SWEEP_Z_CONV };
+
 template <int N>
-void launch_pass(float2* data, int batch, int kind, int mode, const float2* tw, const void* green,
-                 hipStream_t s) {
-    constexpr int W = pencils<N>();
-    const unsigned blocks = (unsigned)((int64_t)N * N / W);
-    dim3 grid(blocks, batch), block(kFftThreads);
+void launch_sweep(float2* data, int batch, Sweep what, const float2* tw, const double* green, hipStream_t s) {
+    const dim3 grid((unsigned)((int64_t)N * N / pencils<N>()), batch), block(kFftThreads);
 #define CUBE_L(K, MO) hipLaunchKernelGGL((k_fft<N, K, MO>), grid, block, 0, s, data, tw, green)
-    if (kind == 0) {
-        if (mode == 0) CUBE_L(0, 0); else CUBE_L(0, 1);
-    } else if (kind == 1) {
-        if (mode == 0) CUBE_L(1, 0); else CUBE_L(1, 1);
+    if (what == SWEEP_Z) { CUBE_L(2, 0); return; }
+    if (what == SWEEP_Z_INV) { CUBE_L(2, 1); return; }
+    if (what == SWEEP_Z_CONV) { CUBE_L(2, 2); return; }
+    if constexpr (N <= kPlaneMax) {
+        const dim3 planes(N, batch), threads(xy_threads<N>());
+        if (what == SWEEP_XY) hipLaunchKernelGGL((k_fft_xy<N, false, false>), planes, threads, 0, s, data, tw);
+        else if (what == SWEEP_XY_INV) hipLaunchKernelGGL((k_fft_xy<N, true, false>), planes, threads, 0, s, data, tw);
+        else hipLaunchKernelGGL((k_fft_xy<N, true, true>), planes, threads, 0, s, data, tw);
     } else {
-        if (mode == 0) CUBE_L(2, 0);
-        else if (mode == 1) CUBE_L(2, 1);
-        else if (mode == 2) CUBE_L(2, 2);
-        else CUBE_L(2, 3);
+        if (what == SWEEP_XY) { CUBE_L(0, 0); CUBE_L(1, 0); }
+        else if (what == SWEEP_XY_INV) { CUBE_L(0, 1); CUBE_L(1, 1); }
+        else { CUBE_L(1, 1); CUBE_L(0, 1); }
     }
 #undef CUBE_L
 }
 
-using PassFn = void (*)(float2*, int, int, int, const float2*, const void*, hipStream_t);
+using SweepFn = void (*)(float2*, int, Sweep, const float2*, const double*, hipStream_t);
 
-PassFn pass_for(int n) {
+SweepFn sweep_for(int n) {
     switch (n) {
-        case 16: return launch_pass<16>;
-        case 32: return launch_pass<32>;
-        case 48: return launch_pass<48>;
-        case 64: return launch_pass<64>;
-        case 80: return launch_pass<80>;
-        case 96: return launch_pass<96>;
-        case 112: return launch_pass<112>;
-        case 128: return launch_pass<128>;
-        case 160: return launch_pass<160>;
-        case 192: return launch_pass<192>;
-        case 224: return launch_pass<224>;
-        case 256: return launch_pass<256>;
-        case 320: return launch_pass<320>;
-        case 384: return launch_pass<384>;
-        case 448: return launch_pass<448>;
-        case 512: return launch_pass<512>;
-        case 1024: return launch_pass<1024>;
+        case 16: return launch_sweep<16>;
+        case 32: return launch_sweep<32>;
+        case 48: return launch_sweep<48>;
+        case 64: return launch_sweep<64>;
+        case 80: return launch_sweep<80>;
+        case 96: return launch_sweep<96>;
+        case 112: return launch_sweep<112>;
+        case 128: return launch_sweep<128>;
+        case 160: return launch_sweep<160>;
+        case 192: return launch_sweep<192>;
+        case 224: return launch_sweep<224>;
+        case 256: return launch_sweep<256>;
+        case 320: return launch_sweep<320>;
+        case 384: return launch_sweep<384>;
+        case 448: return launch_sweep<448>;
+        case 512: return launch_sweep<512>;
+        case 1024: return launch_sweep<1024>;
         default: return nullptr;
     }
 }
 
 }  // namespace
 
-bool fft_supported(int n) { return pass_for(n) != nullptr; }
+bool fft_supported(int n) { return sweep_for(n) != nullptr; }
 
 bool fft_tiles_supported(int n) { return tiles_for(n) != nullptr; }
 
@@ -1089,27 +1125,16 @@ void fft_make_twiddles(int n, float2* dev_table, hipStream_t s) {
 }
 
 void fft3d(float2* data, int n, int batch, bool inverse, const float2* tw, hipStream_t s) {
-    PassFn f = pass_for(n);
-    const int mode = inverse ? 1 : 0;
-    f(data, batch, 0, mode, tw, nullptr, s);
-    f(data, batch, 1, mode, tw, nullptr, s);
-    f(data, batch, 2, mode, tw, nullptr, s);
+    SweepFn f = sweep_for(n);
+    f(data, batch, inverse ? SWEEP_XY_INV : SWEEP_XY, tw, nullptr, s);
+    f(data, batch, inverse ? SWEEP_Z_INV : SWEEP_Z, tw, nullptr, s);
 }
 
-void fft3d_convolve(float2* data, int n, int batch, const float2* tw, const void* green_octant, int table_kind,
-                    hipStream_t s, hipEvent_t* ev) {
-    PassFn f = pass_for(n);
-    if (ev) hipEventRecord(ev[0], s);
-    f(data, batch, 0, 0, tw, nullptr, s);
-    if (ev) hipEventRecord(ev[1], s);
-    f(data, batch, 1, 0, tw, nullptr, s);
-    if (ev) hipEventRecord(ev[2], s);
-    f(data, batch, 2, table_kind == 0 ? 2 : 3, tw, green_octant, s);
-    if (ev) hipEventRecord(ev[3], s);
-    f(data, batch, 1, 1, tw, nullptr, s);
-    if (ev) hipEventRecord(ev[4], s);
-    f(data, batch, 0, 1, tw, nullptr, s);
-    if (ev) hipEventRecord(ev[5], s);
+void fft3d_convolve(float2* data, int n, int batch, const float2* tw, const double* green_octant, hipStream_t s) {
+    SweepFn f = sweep_for(n);
+    f(data, batch, SWEEP_XY, tw, nullptr, s);
+    f(data, batch, SWEEP_Z_CONV, tw, green_octant, s);
+    f(data, batch, SWEEP_YX_INV, tw, nullptr, s);
 }
 
 }  // namespace cube

@@ -186,11 +186,8 @@ void fft_make_twiddles(int n, float2* dev_table, hipStream_t s);
 std::vector<float2> fft_twiddles(int n);
 // Forward or inverse 3-D transform of `batch` cubes of side n.
 void fft3d(float2* data, int n, int batch, bool inverse, const float2* tw, hipStream_t s);
-// Forward 3-D, multiply by a real octant Green's table, inverse 3-D.
-// table_kind: 0 = float octant (n/2+1)^3, 1 = double octant.
-// ev (optional, 6 events): recorded before the first pass and after each pass.
-void fft3d_convolve(float2* data, int n, int batch, const float2* tw, const void* green_octant,
-                    int table_kind, hipStream_t s, hipEvent_t* ev = nullptr);
+// Forward 3-D, multiply by a real octant Green's table (n/2+1)^3, inverse 3-D.
+void fft3d_convolve(float2* data, int n, int batch, const float2* tw, const double* green_octant, hipStream_t s);
 
 // Real tile meshes (ntiles cubes of n^3 floats, [z][y][x]) -> convolution with
 // a real even octant table (pencil-major, as build_fine_green writes it) through half spectra (n^2 (n/2+1) complex per
