@@ -24,7 +24,8 @@ __device__ inline int wave_inclusive_scan(int v) {
 
 // Exclusive scan over the whole block (blockDim.x a multiple of 64, <= 1024).
 // lds needs blockDim.x / 64 + 1 ints.  Returns the exclusive prefix of v and
-// writes the block total to *total.
+// writes the block total to *total.  Every thread adds up the wave totals
+// itself (broadcast reads in flight together) instead of waiting for one.
 __device__ inline int block_exclusive_scan(int v, int* lds, int* total) {
     const int lane = threadIdx.x & (kWave - 1);
     const int wid = threadIdx.x / kWave;
@@ -32,25 +33,16 @@ __device__ inline int block_exclusive_scan(int v, int* lds, int* total) {
     int inc = wave_inclusive_scan(v);
     if (lane == kWave - 1) lds[wid] = inc;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        int acc = 0;
-        for (int w = 0; w < nw; ++w) {
-            int t = lds[w];
-            lds[w] = acc;
-            acc += t;
-        }
-        lds[nw] = acc;
+    int before = 0, all = 0;
+    for (int w = 0; w < nw; ++w) {
+        const int t = lds[w];
+        before += w < wid ? t : 0;
+        all += t;
     }
+    *total = all;
     __syncthreads();
-    int res = inc - v + lds[wid];
-    *total = lds[nw];
-    __syncthreads();
-    return res;
+    return inc - v + before;
 }
-
-// The same scan with barriers that order LDS alone, for callers whose global
-// stores still in flight need not complete first.  Defined after lds_barrier.
-__device__ inline int block_exclusive_scan_lds(int v, int* lds, int* total);
 
 __device__ inline int wave_max(int v) {
 #pragma unroll
@@ -68,6 +60,17 @@ __device__ inline double wave_sum_d(double v) {
 #pragma unroll
     for (int d = kWave / 2; d > 0; d >>= 1) v += __shfl_xor(v, d, kWave);
     return v;
+}
+
+// compute units of the current device (of the first one asked for)
+inline int device_cus() {
+    static const int cus = [] {
+        int dev = 0, v = 0;
+        hipGetDevice(&dev);
+        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) v = 256;
+        return v;
+    }();
+    return cus;
 }
 
 inline unsigned grid1d(int64_t work, int per_block) {
@@ -180,29 +183,6 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-__device__ inline int block_exclusive_scan_lds(int v, int* lds, int* total) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wid = threadIdx.x / kWave;
-    const int nw = blockDim.x / kWave;
-    int inc = wave_inclusive_scan(v);
-    if (lane == kWave - 1) lds[wid] = inc;
-    lds_barrier();
-    if (threadIdx.x == 0) {
-        int acc = 0;
-        for (int w = 0; w < nw; ++w) {
-            int t = lds[w];
-            lds[w] = acc;
-            acc += t;
-        }
-        lds[nw] = acc;
-    }
-    lds_barrier();
-    int res = inc - v + lds[wid];
-    *total = lds[nw];
-    lds_barrier();
-    return res;
 }
 
 }  // namespace cube

@@ -19,6 +19,8 @@
 //
 // The brick kernel serves the periodic single-tile mesh and the diagnostic
 // mesh; tile meshes of a tiled box use the z-marching form further down.
+#include <algorithm>
+
 #include "common.h"
 
 namespace cube {
@@ -213,197 +215,289 @@ __global__ __launch_bounds__(kDepThreads) void k_deposit(Geom g, const int32_t* 
 // it in chunks of CZ fine planes (CZ / cpc coarse layers).  A chunk pulls the
 // particles of its own coarse layers only (with one coarse cell on each side
 // in x and y): its particles reach at most one plane below the chunk and one
-// past it, so the accumulator holds CZ + 2 planes, and the two upper planes
-// stay in LDS as the first two of the next chunk instead of being rebuilt
-// from the layer above.  Per owned cell a chunk reads (BW / cpc + 2)^2 /
-// (BW / cpc)^2 of the particles (1.56x for 32 x 32 columns at cpc = 4)
-// against the brick's (BW / cpc + 2)^3 / (BW / cpc)^3 (3.4x for 16^3 bricks).
-// The weights, the exactness and the single FP32 rounding are those of the
-// brick kernel above.
-template <int BW, int CZ, int NT, int U, class ACC, int MAXSRC, int MAPCAP>
+// past it, so the accumulator is a ring of CZ + 2 planes, of which a chunk
+// finishes CZ.  Per owned cell a chunk reads (BW / cpc + 2)^2 / (BW / cpc)^2
+// of the particles (1.56x for 32 x 32 columns at cpc = 4) against the brick's
+// (BW / cpc + 2)^3 / (BW / cpc)^3 (3.4x for 16^3 bricks).  The weights, the
+// exactness and the single FP32 rounding are those of the brick kernel above.
+//
+// The stores (1.05 GB per 64 tiles of 160^3) take as long as the particles,
+// the LDS atomics next to nothing; in two phases, particles then stores, the
+// times add up (228 us without any particle, 228 for the particles, 456
+// together).  So a chunk is one phase and one barrier, in which a thread
+//   loads U consecutive particles, their cells found by a map of every U-th
+//   particle and the following cells' bounds;
+//   takes its cells of the planes that the previous chunk finished and clears
+//   them for the ring's next turn;
+//   waits for the loads (they and the stores share one in-order counter), then
+//   stores the planes;
+//   adds the particles, eight corners each without bounds checks: rows and
+//   planes have spare cells between them for the corners that fall off the
+//   column (a particle none of whose corners is in it is skipped).
+// The ring holds the CZ planes being written and the CZ + 2 being added to.
+// With eight planes a layer (cpc = 8) that would leave one workgroup per CU:
+// there (TWO) a second phase takes and stores the planes just finished, from a
+// ring of CZ + 2, and issues the next chunk's loads before (500 us as one
+// phase of 1024 threads, 463 as two of 512).
+// Source tables are built two chunks ahead: ranges loaded and counts scanned
+// within the waves in one phase, ranks finished in the next.
+//
+// A column may be cut in z: part i of `parts` finishes the planes of its own
+// chunks and starts one chunk early, whose particles reach its first planes.
+// The launch cuts where workgroups would leave the chip's last round empty
+// (column_parts).  64 tiles of a 1024^3 step: 470 us in two phases and whole
+// columns, 400 now (1.05 GB written, 2.9 TB/s in all); 8 tiles 111 -> 57.
+template <int BW, int CZ, int NT, int U, bool TWO, class ACC, int MAXSRC, int MAPCAP>
 __global__ __launch_bounds__(NT) void k_deposit_zm(Geom g, const int32_t* __restrict__ offsets, Planes p,
                                                     float* __restrict__ out, int cpc, int log2D, double scale,
-                                                    int tile0) {
-    static_assert(MAXSRC <= 1024, "fixed-step search over the source window");
-    static_assert(BW % 4 == 0 && NT % kWave == 0, "float4 rows, whole waves");
-    constexpr int NP = CZ + 2;                   // planes z0 - 1 .. z0 + CZ of chunk z0
-    constexpr int PL = BW * BW;
-    constexpr int kPer = (MAXSRC + NT - 1) / NT;
-    __shared__ __align__(16) ACC acc[NP * PL];
-    __shared__ int s_start[MAXSRC];
-    __shared__ int s_pref[MAXSRC + 1];
-    __shared__ int s_rel[MAXSRC];                // source cell: x, y from the column's ring, z in the chunk; 8 bits each
-    __shared__ uint16_t s_map[MAPCAP];
-    __shared__ int s_scan[NT / kWave + 1];
+                                                    int tile0, int parts) {
+    static_assert(MAXSRC <= NT && MAXSRC <= 256, "a source cell per thread, cells in a byte");
+    static_assert(BW % 4 == 0 && NT % (BW * BW / 4) == 0, "float4 rows, whole planes per pass");
+    // planes z0 - 1 .. z0 + CZ of the chunk at z0, and the CZ before them
+    constexpr int NP = (TWO ? 1 : 2) * CZ + 2;
+    constexpr int RS = BW + 4, PS = (BW + 1) * RS;   // row and plane strides: spare cells at x = -1, BW and y = -1, BW
+    constexpr int OFF = RS + 4;                  // cell (0, 0) of the first plane
+    __shared__ __align__(16) ACC acc[OFF + NP * PS];
+    // the source cells that hold particles, two chunks' tables
+    __shared__ int s_pref[2][MAXSRC + U];        // rank of the cell's first particle
+    __shared__ int2 s_cell[2][MAXSRC];           // first particle minus its rank; coordinates: x, y from the column's ring, z in the chunk
+    __shared__ uint8_t s_map[2][MAPCAP / U];     // cell of every U-th particle
+    constexpr int SWAVES = (MAXSRC + kWave - 1) / kWave;
+    __shared__ int2 s_wave[2][SWAVES];           // a wave's particles and filled cells
 
     const int M = g.F;
     const int nbx = (M + BW - 1) / BW;
     const int64_t lb = xcd_logical_block();
-    const int b = (int)(lb % gridDim.x);        // column within the mesh
+    const int b = (int)(lb % gridDim.x) / parts, part = (int)(lb % gridDim.x) % parts;   // column, its part
     const int ky = (int)(lb / gridDim.x);       // tile within the batch
     const int T0x = (b % nbx) * BW, T0y = (b / nbx) * BW;
     const int bwx = min(BW, M - T0x), bwy = min(BW, M - T0y);
     const int nsx = (bwx + cpc - 1) / cpc + 2, nsy = (bwy + cpc - 1) / cpc + 2;
-    const int S0x = T0x / cpc - 1, S0y = T0y / cpc - 1;
-    const int LC = CZ / cpc;                     // coarse layers per chunk
-    const int nch = (g.Fc + LC - 1) / LC;
+    const int LC = CZ / cpc;                     // coarse layers per chunk (a whole number of chunks per mesh)
+    const int nch = g.Fc / LC, nsrc = nsx * nsy * LC;
+    const int j0 = nch * part / parts, j1 = nch * (part + 1) / parts;   // this part's chunks
     const int tile = tile0 + ky;
     const int tx = tile % g.nt, ty = (tile / g.nt) % g.nt, tz = tile / (g.nt * g.nt);
-    const int box0[3] = {tx * g.Tc - g.hc, ty * g.Tc - g.hc, tz * g.Tc - g.hc};
     float* mesh = out + (int64_t)ky * M * M * M;
 
     static_assert(sizeof(acc) % sizeof(uint4) == 0, "accumulators are cleared 16 bytes at a time");
     for (int i = threadIdx.x; i < (int)(sizeof(acc) / sizeof(uint4)); i += NT)
         reinterpret_cast<uint4*>(acc)[i] = make_uint4(0u, 0u, 0u, 0u);
 
-    // particle ranges of chunk j's source cells, thread-owned runs of kPer
-    int my_st[kPer], my_cnt[kPer];
-    auto fetch = [&](int j) {
-        const int c0 = j * LC, nsz = min(LC, g.Fc - c0);
-        const int nsrc = nsx * nsy * nsz;
-#pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-            const int s = threadIdx.x * kPer + q;
-            my_st[q] = 0;
-            my_cnt[q] = 0;
-            if (s < nsrc) {
-                const int fx = S0x + s % nsx, fy = S0y + (s / nsx) % nsy, fz = c0 + s / (nsx * nsy);
-                if (fx >= 0 && fx < g.Fc && fy >= 0 && fy < g.Fc) {
-                    const int64_t c = canon(g, wrapi(fx + box0[0], g.Nc), wrapi(fy + box0[1], g.Nc),
-                                            wrapi(fz + box0[2], g.Nc));
-                    my_st[q] = offsets[c];
-                    my_cnt[q] = offsets[c + 1] - my_st[q];
-                }
-            }
+    // this thread's source cell in every chunk: its column is fixed
+    const int t = threadIdx.x, sx = t % nsx, sy = t / nsx % nsy, sz = t / (nsx * nsy);
+    const int fx = T0x / cpc - 1 + sx, fy = T0y / cpc - 1 + sy;
+    const bool source = t < nsrc && fx >= 0 && fx < g.Fc && fy >= 0 && fy < g.Fc;
+    const int gx = wrapi(fx + tx * g.Tc - g.hc, g.Nc), gy = wrapi(fy + ty * g.Tc - g.hc, g.Nc);
+    const int gz0 = wrapi(sz + tz * g.Tc - g.hc, g.Nc);
+    int my_st = 0, my_cnt = 0;
+    auto fetch = [&](int j) {                    // particle range of chunk j's source cell
+        my_st = my_cnt = 0;
+        if (source && j >= 0 && j < j1) {
+            int cz = gz0 + j * LC;               // below 2 Nc: the tile box is no larger than the mesh
+            cz = cz >= g.Nc ? cz - g.Nc : cz;
+            const int64_t c = canon(g, gx, gy, cz);
+            my_st = offsets[c];
+            my_cnt = offsets[c + 1] - my_st;
         }
     };
-    fetch(0);
+    // the chunk's table: counts scanned within the waves, then (after a
+    // barrier) the cells' first ranks; empty cells are left out
+    int tab_st = 0, tab_cnt = 0, tab_incl = 0, tab_slot = 0, my_total = 0, my_cells = 0;
+    auto table_begin = [&](int buf) {
+        tab_st = my_st;
+        tab_cnt = my_cnt;
+        if (t >= SWAVES * kWave) return;
+        tab_incl = wave_inclusive_scan(tab_cnt);
+        const uint64_t filled = __ballot(tab_cnt > 0);
+        tab_slot = __popcll(filled & ((1ull << (t & (kWave - 1))) - 1ull));
+        if ((t & (kWave - 1)) == kWave - 1) s_wave[buf][t / kWave] = make_int2(tab_incl, __popcll(filled));
+    };
+    auto table_end = [&](int buf) {
+        int before = 0, slot = tab_slot, cells = 0;
+        my_total = 0;
+#pragma unroll
+        for (int w = 0; w < SWAVES; ++w) {
+            const int2 v = s_wave[buf][w];
+            before += w < t / kWave ? v.x : 0;
+            slot += w < t / kWave ? v.y : 0;
+            my_total += v.x;
+            cells += v.y;
+        }
+        const int first = before + tab_incl - tab_cnt;
+        if (tab_cnt > 0) {
+            s_pref[buf][slot] = first;
+            s_cell[buf][slot] = make_int2(tab_st - first, sx | (sy << 8) | (sz << 16));
+            if (my_total <= MAPCAP)
+                for (int e = (first + U - 1) / U; U * e < first + tab_cnt; ++e) s_map[buf][e] = (uint8_t)slot;
+        }
+        if (t < U) s_pref[buf][cells + t] = my_total;
+        my_cells = cells;
+    };
+    static_assert(MAXSRC <= NT, "a thread per source cell");
+    // in-cell bytes and cells (-1: none) of particles e0 .. e0 + U - 1 of a chunk;
+    // every lane loads, so that the wait counts stay exact
+    auto load = [&](int buf, int total, int cells, int e0, uint32_t mm[U][3], int rel[U]) {
+        const int* pref = s_pref[buf];
+        // past the end: the last particle's cell, read and dropped
+        const int end = max(total - 1, 0), es = min(e0, end);
+        int c = total <= MAPCAP ? (int)s_map[buf][es / U] : find_cell_fixed<8>(pref, cells, es);
+        c = min(c, max(cells - 1, 0));
+        int bound[U - 1];                        // no cell is empty: U particles are in U cells at most
+#pragma unroll
+        for (int a = 0; a < U - 1; ++a) bound[a] = pref[c + 1 + a];
+        int2 sc[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = min(e0 + u, end);
+            int k = c;
+#pragma unroll
+            for (int a = 0; a < U - 1; ++a) k += bound[a] <= e;
+            sc[u] = s_cell[buf][k];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool live = e0 + u < total;
+            rel[u] = live ? sc[u].y : -1;
+            const uint32_t q = live ? (uint32_t)(sc[u].x + e0 + u) : 0u;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) mm[u][k] = p.m[k][q];
+        }
+    };
 
     const int D = 1 << log2D;
     const int halfD = D >> 1;
     const float scalef = (float)scale;           // a power of two
-    constexpr int Q = BW / 4;
-    for (int j = 0; j < nch; ++j) {
-        const int nsrc = nsx * nsy * min(LC, g.Fc - j * LC);
-        int run = 0;
+    int ring = 0;                                // accumulator plane of z0 - 1 of the chunk being added
+    auto add = [&](const uint32_t m[U], const int rel[U]) {
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-            const int s = threadIdx.x * kPer + q;
-            if (s < nsrc) {
-                s_rel[s] = (s % nsx) | (((s / nsx) % nsy) << 8) | ((s / (nsx * nsy)) << 16);
-                s_start[s] = my_st[q];
-            }
-            run += my_cnt[q];
-        }
-        int total;
-        int base = block_exclusive_scan_lds(run, s_scan, &total);
-        const bool mapped = total <= MAPCAP;
+        for (int u = 0; u < U; ++u) {
+            if (rel[u] < 0) continue;
+            // coarse cell relative to the column's first cell in x and y and
+            // to the chunk's first layer in z
+            const int cell[3] = {(rel[u] & 255) - 1, ((rel[u] >> 8) & 255) - 1, rel[u] >> 16};
+            int i0[3];
+            unsigned w1[3];
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-            const int s = threadIdx.x * kPer + q;
-            if (s < nsrc) {
-                s_pref[s] = base;
-                if (mapped)
-                    for (int e = 0; e < my_cnt[q]; ++e) s_map[base + e] = (uint16_t)s;
+            for (int k = 0; k < 3; ++k) {
+                const int P = 2 * (cell[k] * 256 + (int)((m[u] >> (8 * k)) & 255u)) + 1;   // units of 1/D target cells
+                const int Pm = P - halfD;
+                i0[k] = Pm >> log2D;                                // floor division
+                w1[k] = (unsigned)(Pm & (D - 1));
             }
-            base += my_cnt[q];
+            if ((unsigned)(i0[0] + 1) > (unsigned)BW || (unsigned)(i0[1] + 1) > (unsigned)BW) continue;
+            // weights are at most D <= 128 per axis: 24-bit products
+            const unsigned w0[3] = {(unsigned)D - w1[0], (unsigned)D - w1[1], (unsigned)D - w1[2]};
+            // plane i0 of the chunk is ring plane i0 + 1 after its first
+            int z = ring + i0[2] + 1;
+            z = z >= NP ? z - NP : z;
+            const int z1 = z + 1 == NP ? 0 : z + 1;
+            ACC* at = acc + OFF + i0[1] * RS + i0[0];
+#pragma unroll
+            for (int oz = 0; oz < 2; ++oz) {
+                ACC* pl = at + (oz ? z1 : z) * PS;
+                const unsigned wz = oz ? w1[2] : w0[2];
+                const unsigned wy0 = (unsigned)__umul24(w0[1], wz), wy1 = (unsigned)__umul24(w1[1], wz);
+                atomicAdd(pl, (ACC)(unsigned)__umul24(w0[0], wy0));
+                atomicAdd(pl + 1, (ACC)(unsigned)__umul24(w1[0], wy0));
+                atomicAdd(pl + RS, (ACC)(unsigned)__umul24(w0[0], wy1));
+                atomicAdd(pl + RS + 1, (ACC)(unsigned)__umul24(w1[0], wy1));
+            }
         }
-        if (threadIdx.x == 0) s_pref[nsrc] = total;
-        lds_barrier();
-        // the next chunk's ranges load while this chunk deposits
-        if (j + 1 < nch) fetch(j + 1);
+    };
+    // waits for a batch's loads here: the bytes of a particle in one word
+    auto arrived = [&](const uint32_t mm[U][3], uint32_t m[U]) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            m[u] = mm[u][0] | (mm[u][1] << 8) | (mm[u][2] << 16);
+            asm volatile("" : "+v"(m[u]));
+        }
+    };
 
-        for (int e0 = 0; e0 < total; e0 += NT * U) {
-            int mm[U][3], src_of[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int e = e0 + u * NT + threadIdx.x;
-                src_of[u] = -1;
-                if (e < total) {
-                    const int s = mapped ? (int)s_map[e] : find_cell_fixed<(MAXSRC <= 256 ? 8 : 10)>(s_pref, nsrc, e);
-                    const int pidx = s_start[s] + (e - s_pref[s]);
-                    src_of[u] = s;
-#pragma unroll
-                    for (int k = 0; k < 3; ++k) mm[u][k] = p.m[k][pidx];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int s = src_of[u];
-                if (s < 0) continue;
-                const int rl = s_rel[s];
-                // coarse cell relative to the column's first cell in x and y
-                // and to the chunk's first layer in z
-                const int rel[3] = {(rl & 255) - 1, ((rl >> 8) & 255) - 1, rl >> 16};
-                int i0[3];
-                unsigned w1[3];
-#pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    const int P = 2 * (rel[k] * 256 + mm[u][k]) + 1;   // units of 1/D target cells
-                    const int Pm = P - halfD;
-                    i0[k] = Pm >> log2D;                                // floor division
-                    w1[k] = (unsigned)(Pm & (D - 1));
-                }
-#pragma unroll
-                for (int oz = 0; oz < 2; ++oz) {
-                    // plane i0 + oz of the chunk is accumulator plane i0 + oz + 1, in [0, CZ + 1]
-                    const int iz = i0[2] + oz + 1;
-                    const unsigned wz = oz ? w1[2] : (unsigned)D - w1[2];
-#pragma unroll
-                    for (int oy = 0; oy < 2; ++oy) {
-                        const int iy = i0[1] + oy;
-                        if (iy < 0 || iy >= bwy) continue;
-                        const unsigned wyz = (unsigned)__umul24(oy ? w1[1] : (unsigned)D - w1[1], wz);
-#pragma unroll
-                        for (int ox = 0; ox < 2; ++ox) {
-                            const int ix = i0[0] + ox;
-                            if (ix < 0 || ix >= bwx) continue;
-                            const ACC w = (ACC)(unsigned)__umul24(ox ? w1[0] : (unsigned)D - w1[0], wyz);
-                            if (w) atomicAdd(&acc[(iz * BW + iy) * BW + ix], w);
-                        }
-                    }
-                }
-            }
+    // this thread's four cells of a plane in the write-out
+    constexpr int PT = BW * BW / 4, PER = NT / PT;   // threads per plane, planes per pass
+    static_assert(CZ % PER == 0, "whole passes");
+    const int wx = 4 * (t % (BW / 4)), wy = t / (BW / 4) % BW, wp = t / PT;
+    const bool wlive = wx < bwx && wy < bwy;
+    float* wdst = mesh + (T0x + wx) + (int64_t)M * (T0y + wy);
+    struct alignas(16) Quad {
+        ACC v[4];
+    };
+    // four cells of ring plane q (below 2 NP), cleared for the ring's next turn
+    auto take = [&](int q) {
+        q = q >= NP ? q - NP : q;
+        Quad* a = reinterpret_cast<Quad*>(acc + OFF + q * PS + wy * RS + wx);
+        const Quad s4 = *a;
+        *a = Quad{{0, 0, 0, 0}};
+        const ACC* v = s4.v;
+        if (max(max(v[0], v[1]), max(v[2], v[3])) < (ACC)(1u << 24)) {
+            // the sums and the power-of-two scale are exact in FP32, and
+            // the fused multiply-add rounds once: the FP64 result
+            return make_float4(fmaf((float)v[0], scalef, -1.0f), fmaf((float)v[1], scalef, -1.0f),
+                               fmaf((float)v[2], scalef, -1.0f), fmaf((float)v[3], scalef, -1.0f));
         }
-        lds_barrier();
+        return make_float4((float)fma((double)v[0], scale, -1.0), (float)fma((double)v[1], scale, -1.0),
+                           (float)fma((double)v[2], scale, -1.0), (float)fma((double)v[3], scale, -1.0));
+    };
+    auto put = [&](int z, float4 v) {
+        if (wlive && z >= 0 && z < M) *reinterpret_cast<float4*>(wdst + (int64_t)z * M * M) = v;
+    };
 
-        // planes z0 - 1 .. z0 + CZ - 2 are complete (after the last chunk:
-        // all of them); four x-consecutive cells per float4 store
-        const bool last = j + 1 == nch;
-        const int nl = last ? NP : CZ;
-        for (int i4 = threadIdx.x; i4 < Q * BW * nl; i4 += NT) {
-            const int ix = 4 * (i4 % Q), iy = (i4 / Q) % BW, L = i4 / (Q * BW);
-            const int z = j * CZ - 1 + L;
-            if (ix >= bwx || iy >= bwy || z < 0 || z >= M) continue;
-            const ACC* a = &acc[(L * BW + iy) * BW + ix];
-            float4 v;
-            if (max(max(a[0], a[1]), max(a[2], a[3])) < (ACC)(1u << 24)) {
-                // the sums and the power-of-two scale are exact in FP32, and
-                // the fused multiply-add rounds once: the FP64 result
-                v.x = fmaf((float)a[0], scalef, -1.0f);
-                v.y = fmaf((float)a[1], scalef, -1.0f);
-                v.z = fmaf((float)a[2], scalef, -1.0f);
-                v.w = fmaf((float)a[3], scalef, -1.0f);
-            } else {
-                v.x = (float)fma((double)a[0], scale, -1.0);
-                v.y = (float)fma((double)a[1], scale, -1.0);
-                v.z = (float)fma((double)a[2], scale, -1.0);
-                v.w = (float)fma((double)a[3], scale, -1.0);
-            }
-            const int64_t cell = (int64_t)(T0x + ix) + (int64_t)M * ((T0y + iy) + (int64_t)M * z);
-            *reinterpret_cast<float4*>(mesh + cell) = v;
-        }
-        if (last) break;
-        lds_barrier();
-        // planes z0 + CZ - 1 and z0 + CZ become the next chunk's first two
-        for (int i = threadIdx.x; i < PL; i += NT) {
-            const ACC a0 = acc[CZ * PL + i], a1 = acc[(CZ + 1) * PL + i];
-            acc[i] = a0;
-            acc[PL + i] = a1;
+    // planes finished by chunk c, from ring plane q on; `own`: they are this
+    // part's (chunk j0 - 1 is another's, or none)
+    uint32_t mm[U][3], m[U];
+    int rel[U];
+    auto flush = [&](int c, int q, bool own) {
+        float4 v[CZ / PER];
 #pragma unroll
-            for (int L = 2; L < NP; ++L) acc[L * PL + i] = (ACC)0;
+        for (int i = 0; i < CZ / PER; ++i) v[i] = take(q + i * PER + wp);
+        arrived(mm, m);
+        asm volatile("" : "+v"(my_st), "+v"(my_cnt));
+        if (own) {
+#pragma unroll
+            for (int i = 0; i < CZ / PER; ++i) put(c * CZ - 1 + i * PER + wp, v[i]);
         }
+    };
+    // phase j: particles of chunk j, table of chunk j + 1, ranges of chunk
+    // j + 2, planes of chunk j - 1 (TWO: of chunk j); the first chunk is j0 - 1
+    int total = 0, cells = 0;                    // of chunk j
+    load(0, 0, 0, 0, mm, rel);
+    arrived(mm, m);
+    for (int j = j0 - 3; j <= j1; ++j) {
+        const int buf = j & 1;
+        if (TWO && j == j1) break;
+        fetch(j + 2);
+        if (!TWO) {
+            load(buf, total, cells, U * t, mm, rel);
+            if (j >= j0) flush(j - 1, ring + NP - CZ, j > j0);
+            else arrived(mm, m);
+            if (j == j1) break;
+        }
+        if (j >= j0 - 2) table_end(buf ^ 1);     // of chunk j + 1
+        add(m, rel);
+        for (int e0 = U * NT + U * t; e0 < total; e0 += U * NT) {
+            load(buf, total, cells, e0, mm, rel);
+            arrived(mm, m);
+            add(m, rel);
+        }
+        table_begin(buf);                        // of chunk j + 2
+        if (TWO) {
+            lds_barrier();
+            load(buf ^ 1, my_total, my_cells, U * t, mm, rel);
+            if (j >= j0 - 1) flush(j, ring, j >= j0);
+            else arrived(mm, m);
+        }
+        total = my_total;
+        cells = my_cells;
+        if (j >= j0 - 1) {
+            ring += CZ;
+            ring = ring >= NP ? ring - NP : ring;
+        }
+        lds_barrier();
     }
+    // past the last chunk its upper plane is complete too (the one above lies
+    // outside the mesh)
+    if (j1 == nch && wp == 0) put(M - 1, take(ring));
 }
 
 // The value of the lane whose index differs in bit X (1 or 2), by DPP.
@@ -607,6 +701,45 @@ void launch_coarse_deposit(const Geom& g, const int32_t* offsets, Planes p, floa
     }
 }
 
+namespace {
+
+// Parts that a column is cut in.  A part of n chunks takes about n + 2 phases
+// (its first chunk is another part's last, and the pipeline fills); the chip
+// holds `slots` workgroups at a time, and beyond one round of them the last
+// one is on average little more than half full.  With columns of 40 chunks on
+// 768 slots: 1600 columns (64 tiles of 160^3) 445, 404, 400, 406, 420 us in 1,
+// 2, 3, 4, 6 parts; 200 columns 98, 65, 57, 66, 60; 25 columns 86 us in one
+// part, 21 in 14.
+int column_parts(int64_t columns, int chunks, int slots) {
+    int best = 1;
+    double least = 0.0;
+    for (int s = 1; s <= chunks / 2 && s <= 16; ++s) {
+        const double rounds = (double)(columns * s) / slots;
+        const double cost = (rounds <= 1.0 ? 1.0 : rounds + 0.6) * ((double)chunks / s + 2.0);
+        if (s == 1 || cost < least) {
+            least = cost;
+            best = s;
+        }
+    }
+    return best;
+}
+
+template <int BW, int CZ, int U, class ACC, int MAXSRC>
+void fine_deposit_columns(const Geom& g, const int32_t* offsets, Planes p, int tile0, int ntiles, float* mesh,
+                          double scale, hipStream_t s) {
+    constexpr int NT = 512, MAPCAP = 3072;
+    constexpr bool TWO = CZ == 8;
+    const int nb = (g.F + BW - 1) / BW, chunks = g.F / CZ;
+    // workgroups per CU: ten planes of accumulators each, and the tables
+    constexpr int lds = 10 * (BW + 1) * (BW + 4) * (int)sizeof(ACC) + 6 * 1024;
+    const int slots = device_cus() * std::max(1, 160 * 1024 / lds);
+    const int parts = column_parts((int64_t)nb * nb * ntiles, chunks, slots);
+    hipLaunchKernelGGL((k_deposit_zm<BW, CZ, NT, U, TWO, ACC, MAXSRC, MAPCAP>), dim3(nb * nb * parts, ntiles),
+                       dim3(NT), 0, s, g, offsets, p, mesh, g.r, g.log2D, scale, tile0, parts);
+}
+
+}  // namespace
+
 void launch_fine_deposit(const Geom& g, const int32_t* offsets, Planes p, int tile0, int ntiles,
                          float* mesh, bool wide, hipStream_t s) {
     // every box has r = 4 or r = 8 (the gather's bricks need it)
@@ -625,18 +758,14 @@ void launch_fine_deposit(const Geom& g, const int32_t* offsets, Planes p, int ti
                                offsets, p, mesh, g.F, g.r, log2D, scale, tile0);
         return;
     }
-    // tile meshes:
-    // z-marching columns of 32 x 32 cells in chunks of 8 planes on 512
-    // threads, 4 particles in flight per thread -- the fastest shape measured
-    // at 1024^3 (10 x 10 x 2 source cells per chunk for r = 4, 6 x 6 x 1 for
-    // r = 8)
-    const int nbz = (g.F + 31) / 32;
-    if (wide)
-        hipLaunchKernelGGL((k_deposit_zm<32, 8, 512, 4, unsigned long long, 200, 4096>), dim3(nbz * nbz, ntiles),
-                           dim3(512), 0, s, g, offsets, p, mesh, g.r, log2D, scale, tile0);
-    else
-        hipLaunchKernelGGL((k_deposit_zm<32, 8, 512, 4, unsigned int, 200, 4096>), dim3(nbz * nbz, ntiles),
-                           dim3(512), 0, s, g, offsets, p, mesh, g.r, log2D, scale, tile0);
+    // tile meshes: z-marching columns of 32 x 32 cells, a coarse layer per chunk
+    if (g.r == 4) {
+        if (wide) fine_deposit_columns<32, 4, 2, unsigned long long, 100>(g, offsets, p, tile0, ntiles, mesh, scale, s);
+        else fine_deposit_columns<32, 4, 2, unsigned int, 100>(g, offsets, p, tile0, ntiles, mesh, scale, s);
+    } else {
+        if (wide) fine_deposit_columns<32, 8, 4, unsigned long long, 36>(g, offsets, p, tile0, ntiles, mesh, scale, s);
+        else fine_deposit_columns<32, 8, 4, unsigned int, 36>(g, offsets, p, tile0, ntiles, mesh, scale, s);
+    }
 }
 
 bool fine_deposit_needs_wide(const Geom& g, int max_block8) {

@@ -971,16 +971,6 @@ __global__ __launch_bounds__(kFftThreads) void k_zconv_half(typename SpecStore<F
     if (FMT == SPEC_F16) raise_flag(bad, flag);
 }
 
-int device_cus() {
-    static const int cus = [] {
-        int dev = 0, v = 0;
-        hipGetDevice(&dev);
-        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) v = 256;
-        return v;
-    }();
-    return cus;
-}
-
 template <int N, int FMT>
 void launch_tiles_fmt(float* real_tiles, void* spec, int ntiles, const float2* tw, const float* green,
                       int32_t* flag, int lo, int hi, hipStream_t s, hipEvent_t* ev) {
