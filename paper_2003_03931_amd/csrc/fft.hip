@@ -285,6 +285,25 @@ __device__ __forceinline__ void stockham_pass(float2* lds, const float2* __restr
     lay_sync<L>();
 }
 
+// The first pass of a transform from registers instead of LDS: v[it][r] is
+// element j + r N/R of pencil w of butterfly tid + it NT, as below.
+template <int N, class L, bool INV, int R, int IT>
+__device__ __forceinline__ void first_pass(float2* lds, float2 (&v)[IT][R], int tid) {
+    constexpr int NB = N / R, TOTAL = NB * L::P;
+    static_assert(!L::WFAST && IT == (TOTAL + L::NT - 1) / L::NT, "contiguous pencils");
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        const int b = tid + it * L::NT, j = b % NB, w = b / NB;
+        if (TOTAL % L::NT == 0 || b < TOTAL) {
+            Dft<R, INV>::run(v[it]);
+            float2* col = lds + w * L::SP + j * R * L::SE;
+#pragma unroll
+            for (int r = 0; r < R; ++r) col[r * L::SE] = v[it][r];
+        }
+    }
+    lay_sync<L>();
+}
+
 template <int N, class L, bool INV, int NS>
 __device__ __forceinline__ void run_passes(float2*, const float2*, int, int) {}
 
@@ -297,15 +316,22 @@ __device__ __forceinline__ void run_passes(float2* lds, const float2* __restrict
 // Radix plan per supported size.
 template <int N>
 struct Plan;
-#define CUBE_FFT_PLAN(NN, ...)                                                   \
+#define CUBE_FFT_PLAN(NN, R1, ...)                                               \
     template <>                                                                  \
     struct Plan<NN> {                                                            \
+        static constexpr int FIRST = R1;                                         \
+        template <class L, bool INV>                                             \
+        __device__ __forceinline__ static void run_rest(float2* lds,             \
+                                                        const float2* __restrict__ tw, \
+                                                        int tid, int npen) {     \
+            run_passes<NN, L, INV, R1, __VA_ARGS__>(lds, tw, tid, npen);         \
+        }                                                                        \
         template <class L, bool INV>                                             \
         __device__ __forceinline__ static void run(float2* lds,                  \
                                                    const float2* __restrict__ tw, \
                                                    int tid = threadIdx.x,        \
                                                    int npen = L::P) {            \
-            run_passes<NN, L, INV, 1, __VA_ARGS__>(lds, tw, tid, npen);          \
+            run_passes<NN, L, INV, 1, R1, __VA_ARGS__>(lds, tw, tid, npen);      \
         }                                                                        \
     };
 CUBE_FFT_PLAN(16, 4, 4)
@@ -701,6 +727,17 @@ struct PlaneSplit {
     static constexpr bool ok = HALF % NW == 0;
 };
 
+// Two stored spectrum values, read or written together, and the LDS place of
+// value e of a plane's half spectrum (rows of N/2 + 1 values).
+template <class T>
+struct alignas(2 * sizeof(T)) SpecPair {
+    T a, b;
+};
+template <int N>
+__device__ __forceinline__ int half_index(int e) {
+    return (e / PlaneSplit<N>::NH) * PlaneSplit<N>::RSH + e % PlaneSplit<N>::NH;
+}
+
 template <int N, int FMT>
 __global__ __launch_bounds__(kPlaneThreads) void k_r2c_plane_w(const float* __restrict__ real_tiles,
                                                                typename SpecStore<FMT>::T* __restrict__ spec_tiles,
@@ -709,8 +746,8 @@ __global__ __launch_bounds__(kPlaneThreads) void k_r2c_plane_w(const float* __re
     using S = SpecStore<FMT>;
     using PS = PlaneSplit<N>;
     constexpr int NH = PS::NH, RS = PS::RS, RSH = PS::RSH, RPW = PS::RPW, CPW = PS::CPW;
-    constexpr int EPW = RPW * N;                             // complex elements of a wave's rows
-    constexpr int PER = (EPW + kWave - 1) / kWave;
+    // the rows' first butterflies, loaded as such
+    constexpr int R1 = Plan<N>::FIRST, NB = N / R1, FIRSTS = NB * RPW, PER = (FIRSTS + kWave - 1) / kWave;
     constexpr int KIT = (NH + kWave - 1) / kWave;
     __shared__ float2 lds[PS::HALF * RS];
     __shared__ float2 tw[N];
@@ -718,7 +755,7 @@ __global__ __launch_bounds__(kPlaneThreads) void k_r2c_plane_w(const float* __re
     const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
     const int j0 = wv * RPW;
     const int c0 = wv * CPW, ncol = NH - c0 < CPW ? NH - c0 : CPW;
-    float re[PER], im[PER];
+    float re[PER][R1], im[PER][R1];
     // lane indices pass through an opaque copy per use, so that per-element
     // offsets are recomputed each plane instead of held in registers
     auto prefetch = [&](int pl) {
@@ -730,10 +767,13 @@ __global__ __launch_bounds__(kPlaneThreads) void k_r2c_plane_w(const float* __re
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
             int e = ln + u * kWave;
-            if ((u + 1) * kWave > EPW) e = e < EPW ? e : EPW - 1;
-            const int j = e / N, x = e % N;
-            re[u] = src[(2 * j) * N + x];
-            im[u] = src[(2 * j + 1) * N + x];
+            if ((u + 1) * kWave > FIRSTS) e = e < FIRSTS ? e : FIRSTS - 1;
+            const float* row = src + 2 * (e / NB) * N + e % NB;
+#pragma unroll
+            for (int r = 0; r < R1; ++r) {
+                re[u][r] = row[r * NB];
+                im[u][r] = row[N + r * NB];
+            }
         }
     };
     bool bad = false;
@@ -742,21 +782,26 @@ __global__ __launch_bounds__(kPlaneThreads) void k_r2c_plane_w(const float* __re
     // the first plane's loads are waited for here, so that no path into the
     // loop's top has loads pending and the top never waits
 #pragma unroll
-    for (int u = 0; u < PER; ++u) asm volatile("" ::"v"(re[u]), "v"(im[u]));
+    for (int u = 0; u < PER; ++u)
+#pragma unroll
+        for (int r = 0; r < R1; ++r) asm volatile("" ::"v"(re[u][r]), "v"(im[u][r]));
     for (; plane < nplanes; plane += gridDim.x) {
         lds_barrier();                                     // the previous plane's spectrum is stored
         float2* rows = lds + j0 * RS;
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const int e = lane + u * kWave;
-            if ((u + 1) * kWave <= EPW || e < EPW) rows[(e / N) * RS + e % N] = make_float2(re[u], im[u]);
-        }
-        wave_sync();
-        if (plane + (int)gridDim.x < nplanes) prefetch(plane + gridDim.x);
-        asm volatile("" ::: "memory");                       // keep the prefetch loads here, ahead of the passes
         int tid = lane;
         asm volatile("" : "+v"(tid));
-        Plan<N>::template run<Lay<RPW, 1, RS, false, kWave, true>, false>(rows, tw, tid);
+        using L = Lay<RPW, 1, RS, false, kWave, true>;
+        {
+            float2 v[PER][R1];
+#pragma unroll
+            for (int u = 0; u < PER; ++u)
+#pragma unroll
+                for (int r = 0; r < R1; ++r) v[u][r] = make_float2(re[u][r], im[u][r]);
+            first_pass<N, L, false>(rows, v, tid);
+        }
+        if (plane + (int)gridDim.x < nplanes) prefetch(plane + gridDim.x);
+        asm volatile("" ::: "memory");                       // keep the prefetch loads here, ahead of the passes
+        Plan<N>::template run_rest<L, false>(rows, tw, tid, RPW);
         // A(k) = (Z(k) + conj Z(N-k)) / 2, B(k) = (Z(k) - conj Z(N-k)) / 2i, k = 0..N/2
         for (int j = 0; j < RPW; ++j) {
             float2* row = rows + j * RS;
@@ -791,16 +836,24 @@ __global__ __launch_bounds__(kPlaneThreads) void k_r2c_plane_w(const float* __re
         // the stores, so that the top of the next iteration does not wait
         // for these stores to complete.
 #pragma unroll
-        for (int u = 0; u < PER; ++u) asm volatile("" ::"v"(re[u]), "v"(im[u]));
+        for (int u = 0; u < PER; ++u)
+#pragma unroll
+            for (int r = 0; r < R1; ++r) asm volatile("" ::"v"(re[u][r]), "v"(im[u][r]));
         typename S::T* dst = spec_tiles + (int64_t)(plane / N) * N * N * NH + (int64_t)(plane % N) * N * NH;
-        constexpr int SPT = (N * NH + kPlaneThreads - 1) / kPlaneThreads;
+        // two values per store; a pair may end in the next row
+        constexpr int PAIRS = N * NH / 2, SPT = (PAIRS + kPlaneThreads - 1) / kPlaneThreads;
         int t = threadIdx.x;
         asm volatile("" : "+v"(t));
 #pragma unroll
         for (int u = 0; u < SPT; ++u) {
             const int e = t + u * kPlaneThreads;
-            if ((u + 1) * kPlaneThreads <= N * NH || e < N * NH)
-                dst[e] = S::put(lds[(e / NH) * RSH + e % NH], sc_out, bad);
+            if ((u + 1) * kPlaneThreads <= PAIRS || e < PAIRS) {
+                const int at = half_index<N>(2 * e), next = at + (2 * e % NH == NH - 1 ? RSH - NH + 1 : 1);
+                SpecPair<typename S::T> v;
+                v.a = S::put(lds[at], sc_out, bad);
+                v.b = S::put(lds[next], sc_out, bad);
+                reinterpret_cast<SpecPair<typename S::T>*>(dst)[e] = v;
+            }
         }
     }
     if (FMT == SPEC_F16) raise_flag(bad, flag);
@@ -814,13 +867,13 @@ __global__ __launch_bounds__(kPlaneThreads) void k_c2r_plane_w(const typename Sp
     using S = SpecStore<FMT>;
     using PS = PlaneSplit<N>;
     constexpr int NH = PS::NH, RS = PS::RS, RSH = PS::RSH, RPW = PS::RPW, CPW = PS::CPW, HALF = PS::HALF;
-    constexpr int TOT = N * NH;
-    constexpr int PER = (TOT + kPlaneThreads - 1) / kPlaneThreads;
+    constexpr int PAIRS = N * NH / 2;
+    constexpr int PER = (PAIRS + kPlaneThreads - 1) / kPlaneThreads;
     constexpr int KIT = (N + kWave - 1) / kWave;
     // only the window [lo, hi)^3 of each tile is produced: planes lo..hi-1,
     // and in each plane the rows and columns lo..hi-1
     const int W = hi - lo;
-    __shared__ float2 lds[HALF * RS];
+    __shared__ __align__(16) float2 lds[HALF * RS];
     __shared__ float2 tw[N];
     for (int i = threadIdx.x; i < N; i += kPlaneThreads) tw[i] = tw_g[i];
     const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
@@ -829,13 +882,16 @@ __global__ __launch_bounds__(kPlaneThreads) void k_c2r_plane_w(const typename Sp
     // the wave's real rows [2 j0, 2 j0 + 2 RPW) that fall in the window
     const int ya = 2 * j0 > lo ? 2 * j0 : lo, yb = 2 * (j0 + RPW) < hi ? 2 * (j0 + RPW) : hi;
     const bool rows_live = ya < yb;
-    typename S::T pv[PER];
+    using Pair = SpecPair<typename S::T>;
+    Pair pv[PER];
+    // every thread loads (the last round's idle ones re-read the last pair)
     auto prefetch = [&](int pl) {
-        const typename S::T* src = spec_tiles + (int64_t)(pl / W) * N * N * NH + (int64_t)(lo + pl % W) * N * NH;
+        const Pair* src = reinterpret_cast<const Pair*>(spec_tiles + (int64_t)(pl / W) * N * N * NH +
+                                                        (int64_t)(lo + pl % W) * N * NH);
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
             const int e = threadIdx.x + u * kPlaneThreads;
-            if (TOT % kPlaneThreads == 0 || e < TOT) pv[u] = src[e];
+            pv[u] = src[(u + 1) * kPlaneThreads <= PAIRS || e < PAIRS ? e : PAIRS - 1];
         }
     };
     int plane = blockIdx.x;
@@ -843,13 +899,20 @@ __global__ __launch_bounds__(kPlaneThreads) void k_c2r_plane_w(const typename Sp
     // the first plane's loads are waited for here, so that no path into the
     // loop's top has loads pending and the top never waits
 #pragma unroll
-    for (int u = 0; u < PER; ++u) touch_reg(pv[u]);
+    for (int u = 0; u < PER; ++u) {
+        touch_reg(pv[u].a);
+        touch_reg(pv[u].b);
+    }
     for (; plane < nplanes; plane += gridDim.x) {
         lds_barrier();                                     // the previous plane's rows are stored
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
             const int e = threadIdx.x + u * kPlaneThreads;
-            if (TOT % kPlaneThreads == 0 || e < TOT) lds[(e / NH) * RSH + e % NH] = S::get(pv[u], sc_in);
+            if ((u + 1) * kPlaneThreads <= PAIRS || e < PAIRS) {
+                const int at = half_index<N>(2 * e), next = at + (2 * e % NH == NH - 1 ? RSH - NH + 1 : 1);
+                lds[at] = S::get(pv[u].a, sc_in);
+                lds[next] = S::get(pv[u].b, sc_in);
+            }
         }
         lds_barrier();                                     // the plane's spectrum is in LDS
         if (plane + (int)gridDim.x < nplanes) prefetch(plane + gridDim.x);
@@ -862,7 +925,10 @@ __global__ __launch_bounds__(kPlaneThreads) void k_c2r_plane_w(const typename Sp
         // plane's loads (issued long before) ahead of this plane's stores, so
         // that the top of the next iteration does not wait for the stores.
 #pragma unroll
-        for (int u = 0; u < PER; ++u) touch_reg(pv[u]);
+        for (int u = 0; u < PER; ++u) {
+            touch_reg(pv[u].a);
+            touch_reg(pv[u].b);
+        }
         if (rows_live) {
             float2* rows = lds + j0 * RS;
             // complex row Z(k) = A(k) + i B(k) over k = 0..N-1 (Hermitian extension of A, B)
@@ -889,19 +955,29 @@ __global__ __launch_bounds__(kPlaneThreads) void k_c2r_plane_w(const typename Sp
             }
             Plan<N>::template run<Lay<RPW, 1, RS, false, kWave, true>, true>(rows, tw, tid);
             float* dst = real_tiles + (int64_t)(plane / W) * N * N * N + (int64_t)(lo + plane % W) * N * N;
-            // elements (y, x) of rows [ya, yb), x in [lo, hi), walked with increments
-            int y = ya, x = lo + lane;
-            while (x >= hi) {
-                x -= W;
-                ++y;
-            }
-            while (y < yb) {
-                const float2 v = lds[(y >> 1) * RS + x];
-                dst[y * N + x] = (y & 1) ? v.y : v.x;
-                x += kWave;
-                while (x >= hi) {
-                    x -= W;
-                    ++y;
+            // four x of a complex row at a time, which are four of both its
+            // real rows; the last four of a row may be fewer
+            const int groups = (W + 3) / 4;
+            const float inv_groups = 1.0f / (float)groups;
+            for (int q = lane; q < RPW * groups; q += kWave) {
+                const int j = (int)(((float)q + 0.5f) * inv_groups), x = lo + 4 * (q - j * groups);
+                const int y = 2 * (j0 + j);
+                const float2* row = rows + j * RS + x;
+                float2 v[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) v[k] = row[k];    // (reads past the row's end stay in the plane)
+                float* d = dst + y * N + x;
+                if (x + 4 <= hi) {
+                    typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+                    if (y >= ya && y < yb) *reinterpret_cast<f4*>(d) = f4{v[0].x, v[1].x, v[2].x, v[3].x};
+                    if (y + 1 >= ya && y + 1 < yb) *reinterpret_cast<f4*>(d + N) = f4{v[0].y, v[1].y, v[2].y, v[3].y};
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 3; ++k)
+                        if (x + k < hi) {
+                            if (y >= ya && y < yb) d[k] = v[k].x;
+                            if (y + 1 >= ya && y + 1 < yb) d[N + k] = v[k].y;
+                        }
                 }
             }
         }
