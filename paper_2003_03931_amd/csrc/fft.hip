@@ -243,8 +243,18 @@ __device__ __forceinline__ void lay_sync() {
     else lds_barrier();
 }
 
-template <int N, class L, bool INV, int NS, int R>
-__device__ __forceinline__ void stockham_pass(float2* lds, const float2* __restrict__ tw, int tid, int npen) {
+// Keeps a butterfly's outputs as they are.  put() may branch, and the compiler
+// sinks an output's last addition into its branch, away from the product it
+// forms a multiply-add with: the same transform would round differently.  All
+// of them are held before the first branch.
+__device__ __forceinline__ void hold(float2& a) { asm volatile("" : "+v"(a.x), "+v"(a.y)); }
+
+// The pass with its outputs handed to put(index, pencil, value).  SYNC: the
+// outputs go to the same LDS, so every butterfly has been read before, and
+// everything is written when it returns.
+template <int N, class L, bool INV, int NS, int R, bool SYNC, class Put>
+__device__ __forceinline__ void stockham_pass_to(const float2* lds, const float2* __restrict__ tw, int tid, int npen,
+                                                 Put put) {
     constexpr int NB = N / R;
     constexpr int TOTAL = NB * L::P;
     constexpr int IT = (TOTAL + L::NT - 1) / L::NT;
@@ -267,22 +277,31 @@ __device__ __forceinline__ void stockham_pass(float2* lds, const float2* __restr
                 }
             }
             Dft<R, INV>::run(v[it]);
+            if (!SYNC) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) hold(v[it][r]);
+            }
         }
     }
-    lay_sync<L>();
+    if (SYNC) lay_sync<L>();
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
         const int b = tid + it * L::NT;
         const int j = L::WFAST ? b / L::P : b % NB;
         const int w = L::WFAST ? b % L::P : b / NB;
         if ((TOTAL % L::NT == 0 || b < TOTAL) && (!L::WAVE || w < npen)) {
-            const int k = j % NS;
-            float2* col = lds + w * L::SP + ((j / NS) * NS * R + k) * L::SE;
+            const int k = j % NS, first = (j / NS) * NS * R + k;
 #pragma unroll
-            for (int r = 0; r < R; ++r) col[r * NS * L::SE] = v[it][r];
+            for (int r = 0; r < R; ++r) put(first + r * NS, w, v[it][r]);
         }
     }
-    lay_sync<L>();
+    if (SYNC) lay_sync<L>();
+}
+
+template <int N, class L, bool INV, int NS, int R>
+__device__ __forceinline__ void stockham_pass(float2* lds, const float2* __restrict__ tw, int tid, int npen) {
+    stockham_pass_to<N, L, INV, NS, R, true>(lds, tw, tid, npen,
+                                             [&](int i, int w, float2 v) { lds[w * L::SP + i * L::SE] = v; });
 }
 
 // The first pass of a transform from registers instead of LDS: v[it][r] is
@@ -290,10 +309,12 @@ __device__ __forceinline__ void stockham_pass(float2* lds, const float2* __restr
 template <int N, class L, bool INV, int R, int IT>
 __device__ __forceinline__ void first_pass(float2* lds, float2 (&v)[IT][R], int tid) {
     constexpr int NB = N / R, TOTAL = NB * L::P;
-    static_assert(!L::WFAST && IT == (TOTAL + L::NT - 1) / L::NT, "contiguous pencils");
+    static_assert(IT == (TOTAL + L::NT - 1) / L::NT, "a thread's butterflies");
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
-        const int b = tid + it * L::NT, j = b % NB, w = b / NB;
+        const int b = tid + it * L::NT;
+        const int j = L::WFAST ? b / L::P : b % NB;
+        const int w = L::WFAST ? b % L::P : b / NB;
         if (TOTAL % L::NT == 0 || b < TOTAL) {
             Dft<R, INV>::run(v[it]);
             float2* col = lds + w * L::SP + j * R * L::SE;
@@ -313,6 +334,17 @@ __device__ __forceinline__ void run_passes(float2* lds, const float2* __restrict
     run_passes<N, L, INV, NS * R, Rest...>(lds, tw, tid, npen);
 }
 
+// The passes with the outputs of the last one handed on (see stockham_pass_to).
+template <int N, class L, bool INV, int NS, bool SYNC, class Put, int R, int... Rest>
+__device__ __forceinline__ void run_passes_to(float2* lds, const float2* __restrict__ tw, int tid, Put put) {
+    if constexpr (sizeof...(Rest) == 0) {
+        stockham_pass_to<N, L, INV, NS, R, SYNC>(lds, tw, tid, L::P, put);
+    } else {
+        stockham_pass<N, L, INV, NS, R>(lds, tw, tid, L::P);
+        run_passes_to<N, L, INV, NS * R, SYNC, Put, Rest...>(lds, tw, tid, put);
+    }
+}
+
 // Radix plan per supported size.
 template <int N>
 struct Plan;
@@ -325,6 +357,18 @@ struct Plan;
                                                         const float2* __restrict__ tw, \
                                                         int tid, int npen) {     \
             run_passes<NN, L, INV, R1, __VA_ARGS__>(lds, tw, tid, npen);         \
+        }                                                                        \
+        template <class L, bool INV, bool SYNC, class Put>                       \
+        __device__ __forceinline__ static void run_rest_to(float2* lds,          \
+                                                           const float2* __restrict__ tw, \
+                                                           int tid, Put put) {   \
+            run_passes_to<NN, L, INV, R1, SYNC, Put, __VA_ARGS__>(lds, tw, tid, put); \
+        }                                                                        \
+        template <class L, bool INV, bool SYNC, class Put>                       \
+        __device__ __forceinline__ static void run_to(float2* lds,               \
+                                                      const float2* __restrict__ tw, \
+                                                      int tid, Put put) {        \
+            run_passes_to<NN, L, INV, 1, SYNC, Put, R1, __VA_ARGS__>(lds, tw, tid, put); \
         }                                                                        \
         template <class L, bool INV>                                             \
         __device__ __forceinline__ static void run(float2* lds,                  \
@@ -352,13 +396,6 @@ CUBE_FFT_PLAN(448, 7, 8, 8)
 CUBE_FFT_PLAN(512, 8, 8, 8)
 CUBE_FFT_PLAN(1024, 4, 4, 8, 8)
 #undef CUBE_FFT_PLAN
-
-// Plan of the z-pencil pass (16 pencils per 256-thread workgroup): the same
-// radices.  At N = 160 the 10 x 16 plan takes one radix-10 and 5/8 of a
-// radix-16 butterfly per thread and crosses LDS once less than 5, 4, 8 with
-// every thread busy (31.7 against 33.7 ms per 1024^3 step).
-template <int N>
-struct PlanZ : Plan<N> {};
 
 template <int N>
 constexpr int pencils() { return N <= 256 ? 16 : 8; }
@@ -985,7 +1022,13 @@ __global__ __launch_bounds__(kPlaneThreads) void k_c2r_plane_w(const typename Sp
 }
 
 // z pencils of the half spectrum: forward, times G (float octant), inverse.
-// Twiddles and the block's Green's values are staged in LDS with the data.
+// Twiddles and the block's Green's values are staged in LDS.  The data crosses
+// LDS once between passes and no more: the first butterflies are loaded from
+// the spectrum (16 consecutive pencils per kz, whole lines), the last forward
+// outputs are multiplied by G as they are written, and the last inverse ones
+// are stored to the spectrum (494 us per 64 tiles of 160^3 with a stage and
+// loops of their own for these, 440 now).  10 x 16 at 160 points crosses LDS
+// once less than 5, 4, 8.
 template <int N, int FMT>
 __global__ __launch_bounds__(kFftThreads) void k_zconv_half(typename SpecStore<FMT>::T* __restrict__ spec_tiles,
                                                             const float2* __restrict__ tw_g,
@@ -999,7 +1042,7 @@ __global__ __launch_bounds__(kFftThreads) void k_zconv_half(typename SpecStore<F
     constexpr int W = 16;
     constexpr int LDN = N + 1;
     constexpr int PLANE = N * NH;
-    constexpr int U = (W * N + ZT - 1) / ZT < 10 ? (W * N + ZT - 1) / ZT : 10;
+    constexpr int R1 = Plan<N>::FIRST, NB = N / R1, PER = (NB * W + ZT - 1) / ZT;   // first butterflies of a thread
     __shared__ float2 lds[W * LDN];
     __shared__ float2 tw[N];
     __shared__ float gl[W * NH];                   // G of this block's (ky, kx) pencils, by folded kz
@@ -1014,36 +1057,26 @@ __global__ __launch_bounds__(kFftThreads) void k_zconv_half(typename SpecStore<F
         const int ky = c / NH, kx = c - ky * NH;
         gl[e] = green[((int64_t)fold(ky, N) * NH + kx) * NH + fz];
     }
-    // element e: pencil w = e % W, kz = e / W (16 consecutive words per kz)
-    for (int base = 0; base < W * N; base += ZT * U) {
-        T tmp[U];
+    using L = Lay<W, 1, LDN, true, ZT>;            // consecutive threads: consecutive pencils
+    const int tid = threadIdx.x;
+    float2 v[PER][R1];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int e = base + u * ZT + (int)threadIdx.x;
-            if (e < W * N) tmp[u] = g[(int64_t)(e / W) * PLANE + (e % W)];
-        }
+    for (int u = 0; u < PER; ++u) {
+        const int b = tid + u * ZT, j = b / W, w = b % W;
+        if (NB * W % ZT == 0 || b < NB * W) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int e = base + u * ZT + (int)threadIdx.x;
-            if (e < W * N) lds[(e % W) * LDN + e / W] = S::get(tmp[u], sc_in);
+            for (int r = 0; r < R1; ++r) v[u][r] = S::get(g[(int64_t)(j + r * NB) * PLANE + w], sc_in);
         }
     }
-    lds_barrier();
-    using L = Lay<W, 1, LDN, false, ZT>;
-    PlanZ<N>::template run<L, false>(lds, tw);
-    for (int e = threadIdx.x; e < W * N; e += ZT) {
-        const int w = e % W, i = e / W;
+    first_pass<N, L, false>(lds, v, tid);          // (its barrier also covers the tables)
+    Plan<N>::template run_rest_to<L, false, true>(lds, tw, tid, [&](int i, int w, float2 a) {
         const float gv = gl[w * NH + fold(i, N)];
-        const float2 v = lds[w * LDN + i];
-        lds[w * LDN + i] = make_float2(v.x * gv, v.y * gv);
-    }
-    lds_barrier();
-    PlanZ<N>::template run<L, true>(lds, tw);
+        lds[w * LDN + i] = make_float2(a.x * gv, a.y * gv);
+    });
     bool bad = false;
-    for (int e = threadIdx.x; e < W * (hi - lo); e += ZT) {       // only z in [lo, hi) is used
-        const int w = e % W, i = lo + e / W;
-        g[(int64_t)i * PLANE + w] = S::put(lds[w * LDN + i], sc_out, bad);
-    }
+    Plan<N>::template run_to<L, true, false>(lds, tw, tid, [&](int i, int w, float2 a) {
+        if (i >= lo && i < hi) g[(int64_t)i * PLANE + w] = S::put(a, sc_out, bad);   // only z in [lo, hi) is used
+    });
     if (FMT == SPEC_F16) raise_flag(bad, flag);
 }
 
