@@ -20,12 +20,24 @@
 // One workgroup per x-row of Tc coarse cells of a tile (a contiguous run of
 // the canonical order).  It first stages the packed positions of the 3 x 3
 // neighbouring rows, Tc + 2 cells each, in LDS (one coalesced pass; a row's
-// middle Tc cells are one particle range); per axis a thread then visits its
-// own cell and the neighbour on the side its r_pp sphere reaches, reading the
-// partners from LDS.  A workgroup whose neighbourhood holds more than kPPCap
-// particles reads them from global memory instead.  The accelerations go to
-// three FP32 planes in canonical order, which the gather adds to the mesh
-// force before the kick.
+// middle Tc cells are one particle range); a thread then walks, per row its
+// r_pp sphere reaches, the contiguous run of the cells it reaches along x.
+// A row whose neighbourhood exceeds the kPPCap particles of the stage is cut
+// into pieces that fit (at 64 particles a cell no row of 8 cells did, and all
+// pairs were read from global memory: forces of 128^3 particles at r = 8 with
+// r_pp = 2 and 8 fine cells 2500 and 4398 us, 1037 and 4375 now).
+//
+// Bound by instruction issue (0.99 vector instructions per clock and CU, half
+// of the lanes at work).  One particle in six of a neighbourhood is in reach,
+// yet some lane of a wave is at almost every step, so a single loop computes
+// the weight at every step.  Here the loop over partners only measures
+// distances and lists the pairs in reach; the weights are computed from the
+// lists, in the order the pairs were met (96^3 particles, r_pp = 4 fine cells:
+// 240 us -> 207; with lists of 24 or 32 pairs 4 and 13 % more).
+//
+// A single cell whose neighbourhood does not fit reads it from global memory.
+// The accelerations go to three FP32 planes in canonical order, which the
+// gather adds to the mesh force before the kick.
 #include <cmath>
 
 #include "common.h"
@@ -38,6 +50,9 @@ typedef short v2i16 __attribute__((ext_vector_type(2)));
 
 constexpr int kPPThreads = 256;
 constexpr int kPPCap = 4096;     // neighbour particles a workgroup stages in LDS
+constexpr int kPPList = 16;      // pairs a thread lists before their weights are computed
+constexpr int kPPPad = 3;        // out-of-reach entries behind each staged row
+static_assert(16 * kPPCap == 65536, "a list entry holds the row and the place in LDS");
 
 struct PPParams {
     int reach;        // r_pp in position quanta: 256 n_pp / r
@@ -53,8 +68,8 @@ struct PPParams {
 // The second line is the outer branch rewritten about xi = 2, where the pair
 // force vanishes to fifth order: evaluated in t it has no FP32 cancellation.
 __device__ __forceinline__ float pp_weight(int r2, const PPParams& P) {
-    const float u2 = (float)r2;                   // exact: r2 < 2^24
-    const float inv_u = rsqrtf(u2);
+    const float u2 = (float)r2;                   // exact: 1 <= r2 < 2^24
+    const float inv_u = __builtin_amdgcn_rsqf(u2);
     const float x = u2 * inv_u * P.two_over;
     float R;
     if (x <= 1.0f) {
@@ -66,18 +81,15 @@ __device__ __forceinline__ float pp_weight(int r2, const PPParams& P) {
     return R * inv_u * inv_u * inv_u;
 }
 
-// partner loop of one neighbour cell: accumulate the pair accelerations of the
-// particles [q0, q1) whose cell sits dx, dy, dz coarse cells away; pos(q)
-// gives their three position bytes
-template <class Pos>
-__device__ __forceinline__ void pp_cell(int q0, int q1, int dx, int dy, int dz, const int m[3], const PPParams& P,
-                                        Pos pos, float& a0, float& a1, float& a2) {
+// partner loop of one neighbour cell in global memory: accumulate the pair
+// accelerations of the particles [q0, q1) whose cell sits dx, dy, dz coarse
+// cells away
+__device__ __forceinline__ void pp_cell(int q0, int q1, int dx, int dy, int dz, const int m[3], const Planes& in,
+                                        const PPParams& P, float& a0, float& a1, float& a2) {
     for (int q = q0; q < q1; ++q) {
-        int mq[3];
-        pos(q, mq);
-        const int sx = 256 * dx + mq[0] - m[0];
-        const int sy = 256 * dy + mq[1] - m[1];
-        const int sz = 256 * dz + mq[2] - m[2];
+        const int sx = 256 * dx + in.m[0][q] - m[0];
+        const int sy = 256 * dy + in.m[1][q] - m[1];
+        const int sz = 256 * dz + in.m[2][q] - m[2];
         const v2i16 xy = {(short)sx, (short)sy};
         const int r2 = __builtin_amdgcn_sdot2(xy, xy, sz * sz, false);
         if (r2 == 0 || r2 >= P.reach2) continue;
@@ -88,8 +100,9 @@ __device__ __forceinline__ void pp_cell(int q0, int q1, int dx, int dy, int dz, 
     }
 }
 
-// Dynamic LDS: own row offsets [Tc + 1], per neighbour row the LDS ranges of
-// its Tc + 2 cells [9][Tc + 3], and up to kPPCap packed positions.
+// Dynamic LDS: own row offsets [Tc + 1], per neighbour row the particles in
+// front of its Tc + 2 cells [9][Tc + 3] and their sum [Tc + 3], up to kPPCap
+// packed positions, the threads' pair lists [kPPList][threads].
 __global__ __launch_bounds__(kPPThreads) void k_pp(Geom g, const int32_t* __restrict__ offsets, Planes in,
                                                   float* __restrict__ ax_out, float* __restrict__ ay_out,
                                                   float* __restrict__ az_out, PPParams P) {
@@ -97,7 +110,9 @@ __global__ __launch_bounds__(kPPThreads) void k_pp(Geom g, const int32_t* __rest
     const int Tc = g.Tc, RW = Tc + 3;
     int* offs = lds;
     int* s_off = offs + (Tc + 1);
-    uint32_t* s_pos = reinterpret_cast<uint32_t*>(s_off + 9 * RW);
+    int* s_sum = s_off + 9 * RW;
+    uint32_t* s_pos = reinterpret_cast<uint32_t*>(s_sum + RW);
+    uint16_t* s_list = reinterpret_cast<uint16_t*>(s_pos + kPPCap) + threadIdx.x;
     // per neighbour row (dy, dz) = (r % 3 - 1, r / 3 - 1): its first middle
     // cell and the global particle ranges of the middle cells and of the
     // cells just left and right of them
@@ -122,81 +137,150 @@ __global__ __launch_bounds__(kPPThreads) void k_pp(Geom g, const int32_t* __rest
         s_rng[r][5] = offsets[cr + 1];
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        int b = 0;
-        for (int r = 0; r < 9; ++r) {
-            s_base[r] = b;
-            b += (s_rng[r][3] - s_rng[r][2]) + (s_rng[r][1] - s_rng[r][0]) + (s_rng[r][5] - s_rng[r][4]);
-        }
-        s_base[9] = b;
+    // s_off: per row, the particles in front of each of its Tc + 2 cells (left
+    // cell, middle cells, right cell); s_sum: their sum over the rows
+    for (int e = threadIdx.x; e < 9 * RW; e += blockDim.x) {
+        const int r = e / RW, i = e - r * RW;
+        const int nl = s_rng[r][3] - s_rng[r][2], nr = s_rng[r][5] - s_rng[r][4];
+        int v = 0;
+        if (i > 0) v = nl + (offsets[s_cm[r] + min(i - 1, Tc)] - s_rng[r][0]) + (i == Tc + 2 ? nr : 0);
+        s_off[e] = v;
     }
     __syncthreads();
-    const bool staged = s_base[9] <= kPPCap;             // uniform over the workgroup
-    if (staged) {
-        // LDS order per row: left cell, middle cells, right cell
-        for (int e = threadIdx.x; e < 9 * RW; e += blockDim.x) {
-            const int r = e / RW, i = e - r * RW;
-            const int nl = s_rng[r][3] - s_rng[r][2];
-            int v;
-            if (i == 0)
-                v = s_base[r];
-            else if (i <= Tc + 1)
-                v = s_base[r] + nl + (offsets[s_cm[r] + (i - 1)] - s_rng[r][0]);
-            else
-                v = s_base[r + 1];
-            s_off[e] = v;
-        }
-        for (int r = 0; r < 9; ++r) {
-            const int nl = s_rng[r][3] - s_rng[r][2], nm = s_rng[r][1] - s_rng[r][0];
-            const int n = s_base[r + 1] - s_base[r];
-            for (int k = threadIdx.x; k < n; k += blockDim.x) {
-                const int q = k < nl ? s_rng[r][2] + k : k < nl + nm ? s_rng[r][0] + (k - nl) : s_rng[r][4] + (k - nl - nm);
-                s_pos[s_base[r] + k] = (uint32_t)in.m[0][q] | ((uint32_t)in.m[1][q] << 8) | ((uint32_t)in.m[2][q] << 16);
+    for (int i = threadIdx.x; i < RW; i += blockDim.x) {
+        int t = 0;
+        for (int r = 0; r < 9; ++r) t += s_off[r * RW + i];
+        s_sum[i] = t;
+    }
+    // The row's cells [x0, x1) at a time, as many as the stage has room for
+    // with the cells around them, in pieces of one length; cell by cell from
+    // global memory where one cell's neighbourhood does not fit.  Uniform over
+    // the workgroup.
+    for (int x0 = 0; x0 < Tc;) {
+        __syncthreads();                                     // the last piece's stage has been read
+        int x1 = x0;
+        while (x1 < Tc && s_sum[x1 + 3] - s_sum[x0] <= kPPCap - 9 * kPPPad) ++x1;
+        const bool staged = x1 > x0;
+        if (staged) {
+            const int pieces = (Tc - x0 + (x1 - x0) - 1) / (x1 - x0);
+            x1 = x0 + (Tc - x0 + pieces - 1) / pieces;
+            if (threadIdx.x == 0) {
+                int b = 0;
+                for (int r = 0; r < 9; ++r) {
+                    s_base[r] = b;
+                    b += s_off[r * RW + x1 + 2] - s_off[r * RW + x0] + kPPPad;
+                }
+                s_base[9] = b;
             }
-        }
-    }
-    __syncthreads();
-    for (int p = offs[0] + threadIdx.x; p < offs[Tc]; p += blockDim.x) {
-        const int j = find_cell(offs, Tc, p);
-        const int c[3] = {ch.cx0 + j, ch.cy, ch.cz};
-        int m[3], lo[3], hi[3];
+            __syncthreads();
+            // four particles of the nine rows' concatenation at a time, their
+            // loads in flight together: 256 i + m along x (i the cell within the
+            // row), the bytes along y and z
+            const int all = s_base[9], step = (int)blockDim.x;
+            for (int e0 = threadIdx.x; e0 < all; e0 += 4 * step) {
+                int b0[4], b1[4], b2[4], row[4], at[4];
+                bool pad[4];
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            m[k] = in.m[k][p];
-            lo[k] = m[k] < P.reach ? -1 : 0;            // the sphere crosses the lower face
-            hi[k] = m[k] + P.reach > 255 ? 1 : 0;       // ... the upper face
-        }
-        float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f;
-        for (int dz = lo[2]; dz <= hi[2]; ++dz) {
-            for (int dy = lo[1]; dy <= hi[1]; ++dy) {
-                const int r = (dz + 1) * 3 + (dy + 1);
-                for (int dx = lo[0]; dx <= hi[0]; ++dx) {
-                    if (staged) {
-                        const int i = r * RW + j + 1 + dx;
-                        pp_cell(s_off[i], s_off[i + 1], dx, dy, dz, m, P,
-                                [&](int q, int* mq) {
-                                    const uint32_t w = s_pos[q];
-                                    mq[0] = (int)(w & 255u);
-                                    mq[1] = (int)((w >> 8) & 255u);
-                                    mq[2] = (int)(w >> 16);
-                                },
-                                a0, a1, a2);
-                    } else {
-                        const int64_t cn = canon(g, wrapi(c[0] + dx, Nc), wrapi(c[1] + dy, Nc), wrapi(c[2] + dz, Nc));
-                        pp_cell(offsets[cn], offsets[cn + 1], dx, dy, dz, m, P,
-                                [&](int q, int* mq) {
-                                    mq[0] = in.m[0][q];
-                                    mq[1] = in.m[1][q];
-                                    mq[2] = in.m[2][q];
-                                },
-                                a0, a1, a2);
+                for (int u = 0; u < 4; ++u) {
+                    const int e = min(e0 + u * step, all - 1);
+                    const int r = find_cell_fixed<4>(s_base, 9, e), k = e - s_base[r] + s_off[r * RW + x0];
+                    const int nl = s_rng[r][3] - s_rng[r][2], nm = s_rng[r][1] - s_rng[r][0];
+                    const int q = k < nl ? s_rng[r][2] + k : k < nl + nm ? s_rng[r][0] + (k - nl) : s_rng[r][4] + (k - nl - nm);
+                    pad[u] = e >= s_base[r + 1] - kPPPad;
+                    row[u] = r;
+                    at[u] = k;
+                    b0[u] = pad[u] ? 0 : in.m[0][q];
+                    b1[u] = pad[u] ? 0 : in.m[1][q];
+                    b2[u] = pad[u] ? 0 : in.m[2][q];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int e = e0 + u * step;
+                    if (e < all) {
+                        const int i = find_cell(s_off + row[u] * RW, Tc + 2, at[u]);
+                        s_pos[e] = pad[u] ? 0xffffu : (uint32_t)(256 * i + b0[u]) | ((uint32_t)b1[u] << 16) | ((uint32_t)b2[u] << 24);
                     }
                 }
             }
+            __syncthreads();
+        } else {
+            ++x1;
         }
-        ax_out[p] = a0 * P.amp;
-        ay_out[p] = a1 * P.amp;
-        az_out[p] = a2 * P.amp;
+        for (int p = offs[x0] + threadIdx.x; p < offs[x1]; p += blockDim.x) {
+            const int j = find_cell(offs, Tc, p);
+            const int c[3] = {ch.cx0 + j, ch.cy, ch.cz};
+            int m[3], lo[3], hi[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                m[k] = in.m[k][p];
+                lo[k] = m[k] < P.reach ? -1 : 0;            // the sphere crosses the lower face
+                hi[k] = m[k] + P.reach > 255 ? 1 : 0;       // ... the upper face
+            }
+            float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f;
+            if (staged) {
+                const int xp = 256 * (j + 1) + m[0];
+                const uint32_t lim = (uint32_t)(P.reach2 - 1);
+                int n = 0;
+                // the weights of the pairs listed so far, in the order they were met
+                const int yp = m[1] + 256, zp = m[2] + 256;       // (dy + 1 and dz + 1 are kept)
+                auto flush = [&]() {
+                    int e = s_list[0];
+                    uint32_t w = s_pos[e & (kPPCap - 1)];
+                    for (int i = 0; i < n;) {
+                        const int sx = (int)(w & 0xffffu) - xp;
+                        const int sy = (int)((w >> 16) & 255u) - yp + 256 * ((e >> 12) & 3);
+                        const int sz = (int)(w >> 24) - zp + 256 * (e >> 14);
+                        ++i;                                      // the next pair's reads in flight
+                        e = s_list[(i & (kPPList - 1)) * kPPThreads];
+                        w = s_pos[e & (kPPCap - 1)];
+                        const float f = pp_weight(__mul24(sx, sx) + __mul24(sy, sy) + __mul24(sz, sz), P);
+                        a0 += f * (float)sx;
+                        a1 += f * (float)sy;
+                        a2 += f * (float)sz;
+                    }
+                    n = 0;
+                };
+                for (int dz = lo[2]; dz <= hi[2]; ++dz) {
+                    const int zd = zp - 256 * (dz + 1);
+                    for (int dy = lo[1]; dy <= hi[1]; ++dy) {
+                        const int r = (dz + 1) * 3 + (dy + 1);
+                        const int* row = s_off + r * RW + j;
+                        const int shift = s_base[r] - s_off[r * RW + x0];
+                        const int tag = ((dz + 1) * 4 + (dy + 1)) * kPPCap;
+                        const int q1 = row[2 + hi[0]] + shift;
+                        const v2i16 own = {(short)xp, (short)(yp - 256 * (dy + 1))};
+                        // (what a group reads past q1 is out of reach: farther
+                        // cells of the row or its padding)
+                        for (int q = row[1 + lo[0]] + shift; q < q1; q += 4) {
+                            uint32_t w[4];
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) w[k] = s_pos[q + k];
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) {
+                                const v2i16 d = __builtin_bit_cast(v2i16, w[k] & 0x00ffffffu) - own;
+                                const int sz = (int)(w[k] >> 24) - zd;
+                                // 0 < r^2 < reach^2 as one comparison
+                                const uint32_t r2 = (uint32_t)__builtin_amdgcn_sdot2(d, d, __mul24(sz, sz) - 1, false);
+                                if (r2 < lim) s_list[n++ * kPPThreads] = (uint16_t)(q + k + tag);
+                            }
+                            if (__any(n > kPPList - 4)) flush();
+                        }
+                    }
+                }
+                flush();
+            } else {
+                for (int dz = lo[2]; dz <= hi[2]; ++dz)
+                    for (int dy = lo[1]; dy <= hi[1]; ++dy)
+                        for (int dx = lo[0]; dx <= hi[0]; ++dx) {
+                            const int64_t cn = canon(g, wrapi(c[0] + dx, Nc), wrapi(c[1] + dy, Nc), wrapi(c[2] + dz, Nc));
+                            pp_cell(offsets[cn], offsets[cn + 1], dx, dy, dz, m, in, P, a0, a1, a2);
+                        }
+            }
+            ax_out[p] = a0 * P.amp;
+            ay_out[p] = a1 * P.amp;
+            az_out[p] = a2 * P.amp;
+        }
+        x0 = x1;
     }
 }
 
@@ -210,7 +294,8 @@ void launch_pp(const Geom& g, const int32_t* offsets, Planes in, float* const ac
     const double q_per_spacing = 256.0 * g.f / g.r;          // 256 / H
     P.amp = (float)(q_per_spacing * q_per_spacing / (4.0 * M_PI * 140.0));
     const int64_t chunks = g.ncells / g.Tc;
-    const size_t lds = sizeof(int) * ((size_t)(g.Tc + 1) + 9 * (size_t)(g.Tc + 3) + kPPCap);
+    const size_t lds = sizeof(int) * ((size_t)(g.Tc + 1) + 10 * (size_t)(g.Tc + 3) + kPPCap) +
+                       sizeof(uint16_t) * (size_t)kPPList * kPPThreads;
     hipLaunchKernelGGL(k_pp, dim3((unsigned)chunks), dim3(kPPThreads), lds, s, g, offsets, in, acc[0], acc[1], acc[2],
                        P);
 }
