@@ -18,14 +18,24 @@
 // exert nothing.
 //
 // One workgroup per x-row of Tc coarse cells of a tile (a contiguous run of
-// the canonical order).  It first stages the packed positions of the 3 x 3
-// neighbouring rows, Tc + 2 cells each, in LDS (one coalesced pass; a row's
-// middle Tc cells are one particle range); a thread then walks, per row its
-// r_pp sphere reaches, the contiguous run of the cells it reaches along x.
-// A row whose neighbourhood exceeds the kPPCap particles of the stage is cut
-// into pieces that fit (at 64 particles a cell no row of 8 cells did, and all
-// pairs were read from global memory: forces of 128^3 particles at r = 8 with
-// r_pp = 2 and 8 fine cells 2500 and 4398 us, 1037 and 4375 now).
+// the canonical order), a particle per thread, 256 consecutive ones at a time.
+// The packed positions of the 3 x 3 neighbouring rows are staged in LDS (a
+// row's middle Tc cells are one particle range); a thread then walks, per row
+// its r_pp sphere reaches, the contiguous run of the cells it reaches along x.
+// All nine rows at their full length where they fit the kPPCap particles of
+// the stage; else for every 256 particles the cells around theirs, as many
+// rows at a time as fit.  64^3 particles, r = 4, r_pp = 4 fine cells, 60 / 115 /
+// 160 / 300 particles in every filled cell: 1.36 / 3.6 / 5.8 / 14 ms; all pairs
+// from global memory 1.6 / 4.0 / 6.3 / 17; pieces of whole cells, which leave
+// lanes idle, and a cell that does not fit by itself, 1.6 / 5.8 / 8.7 / 24.
+//
+// Pairs come from global memory where a row's range alone exceeds the stage
+// and, when the reach is less than a cell, where the rows would take more than
+// kPPGroups stages: most lanes then need half of the rows at most and wait
+// while the others are walked.  460 particles a cell, reaches of 1/4 to 3/4
+// cell: 0.87 to 0.93 of the time above, 1.11 to 1.23 of it in five stages; 300
+// a cell, three stages: 0.4 to 0.9.  With a whole cell's reach every lane needs
+// every row, and staging is faster at any number (0.87 at 600 a cell).
 //
 // Bound by instruction issue (0.99 vector instructions per clock and CU, half
 // of the lanes at work).  One particle in six of a neighbourhood is in reach,
@@ -35,7 +45,6 @@
 // lists, in the order the pairs were met (96^3 particles, r_pp = 4 fine cells:
 // 240 us -> 207; with lists of 24 or 32 pairs 4 and 13 % more).
 //
-// A single cell whose neighbourhood does not fit reads it from global memory.
 // The accelerations go to three FP32 planes in canonical order, which the
 // gather adds to the mesh force before the kick.
 #include <cmath>
@@ -52,6 +61,7 @@ constexpr int kPPThreads = 256;
 constexpr int kPPCap = 4096;     // neighbour particles a workgroup stages in LDS
 constexpr int kPPList = 16;      // pairs a thread lists before their weights are computed
 constexpr int kPPPad = 3;        // out-of-reach entries behind each staged row
+constexpr int kPPGroups = 3;     // stages for one batch's rows, at most, where the reach is less than a cell
 static_assert(16 * kPPCap == 65536, "a list entry holds the row and the place in LDS");
 
 struct PPParams {
@@ -101,8 +111,8 @@ __device__ __forceinline__ void pp_cell(int q0, int q1, int dx, int dy, int dz, 
 }
 
 // Dynamic LDS: own row offsets [Tc + 1], per neighbour row the particles in
-// front of its Tc + 2 cells [9][Tc + 3] and their sum [Tc + 3], up to kPPCap
-// packed positions, the threads' pair lists [kPPList][threads].
+// front of its Tc + 2 cells [9][Tc + 3], up to kPPCap packed positions, the
+// threads' pair lists [kPPList][threads].
 __global__ __launch_bounds__(kPPThreads) void k_pp(Geom g, const int32_t* __restrict__ offsets, Planes in,
                                                   float* __restrict__ ax_out, float* __restrict__ ay_out,
                                                   float* __restrict__ az_out, PPParams P) {
@@ -110,8 +120,7 @@ __global__ __launch_bounds__(kPPThreads) void k_pp(Geom g, const int32_t* __rest
     const int Tc = g.Tc, RW = Tc + 3;
     int* offs = lds;
     int* s_off = offs + (Tc + 1);
-    int* s_sum = s_off + 9 * RW;
-    uint32_t* s_pos = reinterpret_cast<uint32_t*>(s_sum + RW);
+    uint32_t* s_pos = reinterpret_cast<uint32_t*>(s_off + 9 * RW);
     uint16_t* s_list = reinterpret_cast<uint16_t*>(s_pos + kPPCap) + threadIdx.x;
     // per neighbour row (dy, dz) = (r % 3 - 1, r / 3 - 1): its first middle
     // cell and the global particle ranges of the middle cells and of the
@@ -138,7 +147,7 @@ __global__ __launch_bounds__(kPPThreads) void k_pp(Geom g, const int32_t* __rest
     }
     __syncthreads();
     // s_off: per row, the particles in front of each of its Tc + 2 cells (left
-    // cell, middle cells, right cell); s_sum: their sum over the rows
+    // cell, middle cells, right cell)
     for (int e = threadIdx.x; e < 9 * RW; e += blockDim.x) {
         const int r = e / RW, i = e - r * RW;
         const int nl = s_rng[r][3] - s_rng[r][2], nr = s_rng[r][5] - s_rng[r][4];
@@ -147,77 +156,109 @@ __global__ __launch_bounds__(kPPThreads) void k_pp(Geom g, const int32_t* __rest
         s_off[e] = v;
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < RW; i += blockDim.x) {
-        int t = 0;
-        for (int r = 0; r < 9; ++r) t += s_off[r * RW + i];
-        s_sum[i] = t;
-    }
-    // The row's cells [x0, x1) at a time, as many as the stage has room for
-    // with the cells around them, in pieces of one length; cell by cell from
-    // global memory where one cell's neighbourhood does not fit.  Uniform over
-    // the workgroup.
-    for (int x0 = 0; x0 < Tc;) {
-        __syncthreads();                                     // the last piece's stage has been read
-        int x1 = x0;
-        while (x1 < Tc && s_sum[x1 + 3] - s_sum[x0] <= kPPCap - 9 * kPPPad) ++x1;
-        const bool staged = x1 > x0;
-        if (staged) {
-            const int pieces = (Tc - x0 + (x1 - x0) - 1) / (x1 - x0);
-            x1 = x0 + (Tc - x0 + pieces - 1) / pieces;
-            if (threadIdx.x == 0) {
-                int b = 0;
-                for (int r = 0; r < 9; ++r) {
-                    s_base[r] = b;
-                    b += s_off[r * RW + x1 + 2] - s_off[r * RW + x0] + kPPPad;
-                }
-                s_base[9] = b;
+    const int p_begin = offs[0], p_end = offs[Tc];
+    int around = 9 * kPPPad;
+    for (int r = 0; r < 9; ++r) around += s_off[r * RW + Tc + 2];
+    const bool whole = around <= kPPCap;                     // one stage serves the whole row
+
+    // the neighbours of the row's cells [x0, x1) in rows [g0, g1), staged: four
+    // particles of the rows' concatenation at a time, their loads in flight
+    // together: 256 i + m along x (i the cell within the row), the bytes along
+    // y and z
+    auto stage = [&](int g0, int g1, int x0, int x1) {
+        __syncthreads();                                     // the last stage has been read
+        if (threadIdx.x == 0) {
+            int b = 0;
+            for (int r = 0; r < 10; ++r) {
+                s_base[r] = r <= g1 ? b : 1 << 30;
+                if (r >= g0 && r < g1) b += s_off[r * RW + x1 + 2] - s_off[r * RW + x0] + kPPPad;
             }
-            __syncthreads();
-            // four particles of the nine rows' concatenation at a time, their
-            // loads in flight together: 256 i + m along x (i the cell within the
-            // row), the bytes along y and z
-            const int all = s_base[9], step = (int)blockDim.x;
-            for (int e0 = threadIdx.x; e0 < all; e0 += 4 * step) {
-                int b0[4], b1[4], b2[4], row[4], at[4];
-                bool pad[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int e = min(e0 + u * step, all - 1);
-                    const int r = find_cell_fixed<4>(s_base, 9, e), k = e - s_base[r] + s_off[r * RW + x0];
-                    const int nl = s_rng[r][3] - s_rng[r][2], nm = s_rng[r][1] - s_rng[r][0];
-                    const int q = k < nl ? s_rng[r][2] + k : k < nl + nm ? s_rng[r][0] + (k - nl) : s_rng[r][4] + (k - nl - nm);
-                    pad[u] = e >= s_base[r + 1] - kPPPad;
-                    row[u] = r;
-                    at[u] = k;
-                    b0[u] = pad[u] ? 0 : in.m[0][q];
-                    b1[u] = pad[u] ? 0 : in.m[1][q];
-                    b2[u] = pad[u] ? 0 : in.m[2][q];
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int e = e0 + u * step;
-                    if (e < all) {
-                        const int i = find_cell(s_off + row[u] * RW, Tc + 2, at[u]);
-                        s_pos[e] = pad[u] ? 0xffffu : (uint32_t)(256 * i + b0[u]) | ((uint32_t)b1[u] << 16) | ((uint32_t)b2[u] << 24);
-                    }
-                }
-            }
-            __syncthreads();
-        } else {
-            ++x1;
         }
-        for (int p = offs[x0] + threadIdx.x; p < offs[x1]; p += blockDim.x) {
-            const int j = find_cell(offs, Tc, p);
-            const int c[3] = {ch.cx0 + j, ch.cy, ch.cz};
-            int m[3], lo[3], hi[3];
+        __syncthreads();
+        const int all = s_base[g1], step = (int)blockDim.x;
+        for (int e0 = threadIdx.x; e0 < all; e0 += 4 * step) {
+            uint32_t b0[4], b1[4], b2[4];
+            int row[4], at[4];
+            bool pad[4];
 #pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                m[k] = in.m[k][p];
-                lo[k] = m[k] < P.reach ? -1 : 0;            // the sphere crosses the lower face
-                hi[k] = m[k] + P.reach > 255 ? 1 : 0;       // ... the upper face
+            for (int u = 0; u < 4; ++u) {
+                const int e = min(e0 + u * step, all - 1);
+                int r = 0;
+#pragma unroll
+                for (int i = 1; i < 9; ++i) r += e >= s_base[i];
+                const int k = e - s_base[r] + s_off[r * RW + x0];
+                const int nl = s_rng[r][3] - s_rng[r][2], nm = s_rng[r][1] - s_rng[r][0];
+                const int ql = s_rng[r][2] + k, qm = s_rng[r][0] + (k - nl), qr = s_rng[r][4] + (k - nl - nm);
+                pad[u] = e >= s_base[r + 1] - kPPPad;
+                row[u] = r;
+                at[u] = k;
+                // (no branches: the loads of all four are in flight together)
+                const int q = pad[u] ? 0 : k < nl ? ql : k < nl + nm ? qm : qr;
+                b0[u] = in.m[0][q];
+                b1[u] = in.m[1][q];
+                b2[u] = in.m[2][q];
             }
-            float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f;
-            if (staged) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int e = e0 + u * step;
+                // the cell: largest i with s_off[i] <= at, i < Tc + 2 < 128
+                const int* o = s_off + row[u] * RW;
+                int i = 0;
+#pragma unroll
+                for (int half = 64; half > 0; half >>= 1) {
+                    const int v = o[min(i + half, Tc + 2)];
+                    i = (i + half < Tc + 2) & (v <= at[u]) ? i + half : i;
+                }
+                const uint32_t w = (uint32_t)(256 * i) + b0[u] | b1[u] << 16 | b2[u] << 24;
+                if (e < all) s_pos[e] = pad[u] ? 0xffffu : w;
+            }
+        }
+        __syncthreads();
+    };
+
+    // A particle per thread: the loops and their barriers are uniform over the
+    // workgroup.
+    for (int p0 = p_begin; p0 < p_end; p0 += kPPThreads) {
+        int x0 = 0, x1 = Tc;
+        if (!whole) {
+            x0 = find_cell(offs, Tc, p0);
+            x1 = find_cell(offs, Tc, min(p0 + kPPThreads, p_end) - 1) + 1;
+        }
+        const int p = p0 + (int)threadIdx.x;
+        const bool live = p < p_end;
+        const int j = find_cell(offs, Tc, live ? p : p0);
+        const int c[3] = {ch.cx0 + j, ch.cy, ch.cz};
+        int m[3], lo[3], hi[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            m[k] = live ? in.m[k][p] : 0;
+            lo[k] = m[k] < P.reach ? -1 : 0;            // the sphere crosses the lower face
+            hi[k] = m[k] + P.reach > 255 ? 1 : 0;       // ... the upper face
+            if (!live) hi[k] = lo[k] - 1;               // no rows
+        }
+        float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f;
+        // rows that fit the stage together form a group; bit r: one begins at row r
+        unsigned cuts = 0;
+        bool staged = true;
+        if (!whole) {
+            int n = 0;
+#pragma unroll
+            for (int r = 0; r < 9; ++r) {
+                const int len = s_off[r * RW + x1 + 2] - s_off[r * RW + x0] + kPPPad;
+                staged = staged && len <= kPPCap;
+                n += len;
+                if (n > kPPCap) {
+                    cuts |= 1u << r;
+                    n = len;
+                }
+            }
+            staged = staged && (__popc(cuts) < kPPGroups || P.reach == 256);
+        }
+        if (staged) {
+            for (int g0 = 0, g1; g0 < 9; g0 = g1) {
+                const unsigned later = cuts >> (g0 + 1);
+                g1 = later ? g0 + __ffs(later) : 9;
+                if (!whole || p0 == p_begin) stage(g0, g1, x0, x1);
                 const int xp = 256 * (j + 1) + m[0];
                 const uint32_t lim = (uint32_t)(P.reach2 - 1);
                 int n = 0;
@@ -244,6 +285,7 @@ __global__ __launch_bounds__(kPPThreads) void k_pp(Geom g, const int32_t* __rest
                     const int zd = zp - 256 * (dz + 1);
                     for (int dy = lo[1]; dy <= hi[1]; ++dy) {
                         const int r = (dz + 1) * 3 + (dy + 1);
+                        if (r < g0 || r >= g1) continue;
                         const int* row = s_off + r * RW + j;
                         const int shift = s_base[r] - s_off[r * RW + x0];
                         const int tag = ((dz + 1) * 4 + (dy + 1)) * kPPCap;
@@ -268,19 +310,20 @@ __global__ __launch_bounds__(kPPThreads) void k_pp(Geom g, const int32_t* __rest
                     }
                 }
                 flush();
-            } else {
-                for (int dz = lo[2]; dz <= hi[2]; ++dz)
-                    for (int dy = lo[1]; dy <= hi[1]; ++dy)
-                        for (int dx = lo[0]; dx <= hi[0]; ++dx) {
-                            const int64_t cn = canon(g, wrapi(c[0] + dx, Nc), wrapi(c[1] + dy, Nc), wrapi(c[2] + dz, Nc));
-                            pp_cell(offsets[cn], offsets[cn + 1], dx, dy, dz, m, in, P, a0, a1, a2);
-                        }
             }
+        } else {
+            for (int dz = lo[2]; dz <= hi[2]; ++dz)
+                for (int dy = lo[1]; dy <= hi[1]; ++dy)
+                    for (int dx = lo[0]; dx <= hi[0]; ++dx) {
+                        const int64_t cn = canon(g, wrapi(c[0] + dx, Nc), wrapi(c[1] + dy, Nc), wrapi(c[2] + dz, Nc));
+                        pp_cell(offsets[cn], offsets[cn + 1], dx, dy, dz, m, in, P, a0, a1, a2);
+                    }
+        }
+        if (live) {
             ax_out[p] = a0 * P.amp;
             ay_out[p] = a1 * P.amp;
             az_out[p] = a2 * P.amp;
         }
-        x0 = x1;
     }
 }
 
@@ -294,7 +337,7 @@ void launch_pp(const Geom& g, const int32_t* offsets, Planes in, float* const ac
     const double q_per_spacing = 256.0 * g.f / g.r;          // 256 / H
     P.amp = (float)(q_per_spacing * q_per_spacing / (4.0 * M_PI * 140.0));
     const int64_t chunks = g.ncells / g.Tc;
-    const size_t lds = sizeof(int) * ((size_t)(g.Tc + 1) + 10 * (size_t)(g.Tc + 3) + kPPCap) +
+    const size_t lds = sizeof(int) * ((size_t)(g.Tc + 1) + 9 * (size_t)(g.Tc + 3) + kPPCap) +
                        sizeof(uint16_t) * (size_t)kPPList * kPPThreads;
     hipLaunchKernelGGL(k_pp, dim3((unsigned)chunks), dim3(kPPThreads), lds, s, g, offsets, in, acc[0], acc[1], acc[2],
                        P);
