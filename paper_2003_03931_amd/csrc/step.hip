@@ -146,16 +146,19 @@ __global__ __launch_bounds__(256) void k_moments(Geom g, const int32_t* __restri
 
 // The same sums for linear codes v = u s: u and u^2 are summed as integers,
 // four codes per load, and scaled once per workgroup.  Every partial sum is an
-// integer (below 2^45) times a power of two, so the result is the exact one.
+// integer (below 3 x 128^2 x 2^31 < 2^47, and doubles hold those below 2^53)
+// times a power of two, so the result is the exact one.
+// particles: how many the cells hold, all (a multiple of 4) or, in an empty
+// box, none: its planes hold anything.
 constexpr int kMomentThreads = 256;
 
-__global__ __launch_bounds__(kMomentThreads) void k_moments_linear(Planes p, int64_t n4,
+__global__ __launch_bounds__(kMomentThreads) void k_moments_linear(Planes p, const int32_t* __restrict__ particles,
                                                                    const StepScalars* __restrict__ sc,
                                                                    double* __restrict__ partial) {
     __shared__ long long red[4][kMomentThreads / kWave];
+    const int n4 = *particles / 4;
     long long t[4] = {0, 0, 0, 0};
-    for (int64_t i = (int64_t)blockIdx.x * kMomentThreads + threadIdx.x; i < n4;
-         i += (int64_t)gridDim.x * kMomentThreads) {
+    for (int i = (int)blockIdx.x * kMomentThreads + (int)threadIdx.x; i < n4; i += (int)gridDim.x * kMomentThreads) {
         int sq = 0;
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
@@ -322,7 +325,8 @@ void launch_moments(const Geom& g, const int32_t* offsets, Planes p, const StepS
     } else {
         // (the number of particles is a multiple of 64)
         blocks = (int)std::min<int64_t>(std::min(blocks, 1024), (int64_t)grid1d(g.n / 4, kMomentThreads));
-        hipLaunchKernelGGL(k_moments_linear, dim3(blocks), dim3(kMomentThreads), 0, s, p, g.n / 4, sc, partial);
+        hipLaunchKernelGGL(k_moments_linear, dim3(blocks), dim3(kMomentThreads), 0, s, p, offsets + g.ncells, sc,
+                           partial);
     }
     launch_reduce_partials(partial, blocks, 4, out, false, s);
 }
