@@ -283,8 +283,8 @@ void coarse_potential(cube_ctx* c) {
         hipEvent_t e2 = P.mark(c->stream);
         // deposit: complex mesh write + offsets read + 3 position bytes per particle
         P.add(ST_COARSE_DEP, e0, e1, 12.0 * nc3 + 3.0 * (double)g.n);
-        // five read+write sweeps of the complex mesh
-        P.add(ST_COARSE_FFT, e1, e2, 80.0 * nc3);
+        // read+write sweeps of the complex mesh
+        P.add(ST_COARSE_FFT, e1, e2, 16.0 * fft3d_convolve_sweeps(g.Nc) * nc3);
     }
 }
 

@@ -1199,6 +1199,8 @@ SweepFn sweep_for(int n) {
 
 bool fft_supported(int n) { return sweep_for(n) != nullptr; }
 
+int fft3d_convolve_sweeps(int n) { return n <= kPlaneMax ? 3 : 5; }
+
 bool fft_tiles_supported(int n) { return tiles_for(n) != nullptr; }
 
 void fft_tiles_convolve(float* real_tiles, void* spec_tiles, int n, int ntiles, const float2* tw,

@@ -188,6 +188,8 @@ std::vector<float2> fft_twiddles(int n);
 void fft3d(float2* data, int n, int batch, bool inverse, const float2* tw, hipStream_t s);
 // Forward 3-D, multiply by a real octant Green's table (n/2+1)^3, inverse 3-D.
 void fft3d_convolve(float2* data, int n, int batch, const float2* tw, const double* green_octant, hipStream_t s);
+// the times it reads and writes the cubes
+int fft3d_convolve_sweeps(int n);
 
 // Real tile meshes (ntiles cubes of n^3 floats, [z][y][x]) -> convolution with
 // a real even octant table (pencil-major, as build_fine_green writes it) through half spectra (n^2 (n/2+1) complex per
