@@ -276,7 +276,7 @@ void coarse_potential(cube_ctx* c) {
     Profiler& P = c->prof;
     const double nc3 = (double)g.ncells;
     hipEvent_t e0 = P.on ? P.mark(c->stream) : nullptr;
-    launch_coarse_deposit(g, c->offsets, c->A, c->coarse, nullptr, c->stream);
+    launch_coarse_deposit(g, c->offsets, c->A, c->coarse, c->stream);
     hipEvent_t e1 = P.on ? P.mark(c->stream) : nullptr;
     fft3d_convolve(c->coarse, g.Nc, 1, c->tw_coarse, c->coarse_green, c->stream);
     if (P.on) {
@@ -1098,7 +1098,7 @@ cube_status cube_debug_mesh(cube_ctx* c, int32_t what, int32_t tile, float* out)
     if (!out) return fail(CUBE_INVALID, "null output");
     hipStream_t s = c->stream;
     if (what == 0 || what == 1) {
-        if (what == 0) launch_coarse_deposit(g, c->offsets, c->A, c->coarse, nullptr, s);
+        if (what == 0) launch_coarse_deposit(g, c->offsets, c->A, c->coarse, s);
         else coarse_potential(c);
         CUBE_HIP(hipMemcpy2DAsync(out, sizeof(float), c->coarse, sizeof(float2), sizeof(float), g.ncells,
                                   hipMemcpyDeviceToDevice, s));

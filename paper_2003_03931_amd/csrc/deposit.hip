@@ -27,17 +27,17 @@ namespace cube {
 
 namespace {
 
-enum DepositMode { DEP_COARSE = 0, DEP_FINE_TILED = 1, DEP_FINE_PERIODIC = 2, DEP_DIAG = 3 };
-
 constexpr int kDepThreads = 256;
 
+// A periodic mesh of M^3 cells, cpc of them per coarse cell: the fine mesh of a
+// single periodic tile (real values) or, DIAG, the diagnostic mesh (complex).
 // MAXSRC bounds the source window, (BW / cpc + 2)^3 coarse cells; MAPCAP is
 // the number of window particles whose source cell is looked up from a
 // per-particle map (larger windows fall back to a binary search).
-template <int BW, int MODE, class ACC, int MAXSRC, int MAPCAP>
+template <int BW, bool DIAG, class ACC, int MAXSRC, int MAPCAP>
 __global__ __launch_bounds__(kDepThreads) void k_deposit(Geom g, const int32_t* __restrict__ offsets, Planes p,
                                                           float* __restrict__ out, int M, int cpc, int log2D,
-                                                          double scale, int tile0) {
+                                                          double scale) {
     static_assert(MAXSRC <= 1024, "fixed-step search over the source window");
     __shared__ __align__(16) ACC acc[BW * BW * BW];
     __shared__ int s_start[MAXSRC];
@@ -47,9 +47,7 @@ __global__ __launch_bounds__(kDepThreads) void k_deposit(Geom g, const int32_t* 
     __shared__ int s_scan[kDepThreads / kWave + 1];
 
     const int nbx = (M + BW - 1) / BW;
-    const int64_t lb = xcd_logical_block();
-    const int b = (int)(lb % gridDim.x);        // block within the mesh
-    const int ky = (int)(lb / gridDim.x);       // tile within the batch
+    const int b = (int)xcd_logical_block();
     const int T0[3] = {(b % nbx) * BW, ((b / nbx) % nbx) * BW, (b / (nbx * nbx)) * BW};
     const int bw[3] = {min(BW, M - T0[0]), min(BW, M - T0[1]), min(BW, M - T0[2])};
     int nsa[3];
@@ -58,15 +56,6 @@ __global__ __launch_bounds__(kDepThreads) void k_deposit(Geom g, const int32_t* 
     const int nsrc = nsa[0] * nsa[1] * nsa[2];
     // source frame origin (coarse cells): one cell before the block
     const int S0[3] = {T0[0] / cpc - 1, T0[1] / cpc - 1, T0[2] / cpc - 1};
-
-    int tile = 0, box0[3] = {0, 0, 0};
-    if (MODE == DEP_FINE_TILED) {
-        tile = tile0 + ky;
-        const int tx = tile % g.nt, ty = (tile / g.nt) % g.nt, tz = tile / (g.nt * g.nt);
-        box0[0] = tx * g.Tc - g.hc;
-        box0[1] = ty * g.Tc - g.hc;
-        box0[2] = tz * g.Tc - g.hc;
-    }
 
     static_assert(sizeof(acc) % sizeof(uint4) == 0, "accumulators are cleared 16 bytes at a time");
     for (int i = threadIdx.x; i < (int)(sizeof(acc) / sizeof(uint4)); i += kDepThreads)
@@ -83,23 +72,10 @@ __global__ __launch_bounds__(kDepThreads) void k_deposit(Geom g, const int32_t* 
         if (s < nsrc) {
             const int rx = s % nsa[0], ry = (s / nsa[0]) % nsa[1], rz = s / (nsa[0] * nsa[1]);
             s_rel[s] = rx | (ry << 8) | (rz << 16);
-            int fc[3] = {S0[0] + rx, S0[1] + ry, S0[2] + rz};
-            bool ok = true;
-            if (MODE == DEP_FINE_TILED) {
-#pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    ok = ok && fc[k] >= 0 && fc[k] < g.Fc;
-                    fc[k] += box0[k];
-                }
-            }
-            if (ok) {
-                const int64_t c = canon(g, wrapi(fc[0], g.Nc), wrapi(fc[1], g.Nc), wrapi(fc[2], g.Nc));
-                const int st = offsets[c];
-                cnt = offsets[c + 1] - st;
-                s_start[s] = st;
-            } else {
-                s_start[s] = 0;
-            }
+            const int64_t c = canon(g, wrapi(S0[0] + rx, g.Nc), wrapi(S0[1] + ry, g.Nc), wrapi(S0[2] + rz, g.Nc));
+            const int st = offsets[c];
+            cnt = offsets[c + 1] - st;
+            s_start[s] = st;
         }
         my_cnt[q] = cnt;
         run += cnt;
@@ -177,11 +153,10 @@ __global__ __launch_bounds__(kDepThreads) void k_deposit(Geom g, const int32_t* 
     __syncthreads();
 
     // exact value * scale - 1, rounded once to FP32
-    if (MODE == DEP_FINE_TILED || MODE == DEP_FINE_PERIODIC) {
-        // real mesh of tile ky: four x-consecutive cells per float4 store (the
-        // block origin and the mesh side are multiples of 4, and so is bw[0])
+    if (!DIAG) {
+        // four x-consecutive cells per float4 store (the block origin and the
+        // mesh side are multiples of 4, and so is bw[0])
         constexpr int Q = BW / 4;
-        float* mesh = out + (int64_t)ky * M * M * M;
         for (int i4 = threadIdx.x; i4 < Q * BW * BW; i4 += kDepThreads) {
             const int ix = 4 * (i4 % Q), iy = (i4 / Q) % BW, iz = i4 / (Q * BW);
             if (ix >= bw[0] || iy >= bw[1] || iz >= bw[2]) continue;
@@ -192,7 +167,7 @@ __global__ __launch_bounds__(kDepThreads) void k_deposit(Geom g, const int32_t* 
             v.z = (float)fma((double)a[2], scale, -1.0);
             v.w = (float)fma((double)a[3], scale, -1.0);
             const int64_t cell = (int64_t)(T0[0] + ix) + (int64_t)M * ((T0[1] + iy) + (int64_t)M * (T0[2] + iz));
-            *reinterpret_cast<float4*>(mesh + cell) = v;
+            *reinterpret_cast<float4*>(out + cell) = v;
         }
         return;
     }
@@ -201,12 +176,8 @@ __global__ __launch_bounds__(kDepThreads) void k_deposit(Geom g, const int32_t* 
         if (ix >= bw[0] || iy >= bw[1] || iz >= bw[2]) continue;
         const float v = (float)((double)acc[i] * scale - 1.0);
         const int64_t cell = (int64_t)(T0[0] + ix) + (int64_t)M * ((T0[1] + iy) + (int64_t)M * (T0[2] + iz));
-        if (MODE == DEP_FINE_TILED || MODE == DEP_FINE_PERIODIC) {
-            out[(int64_t)ky * M * M * M + cell] = v;     // real mesh of tile k
-        } else {
-            out[2 * cell] = v;
-            out[2 * cell + 1] = 0.0f;
-        }
+        out[2 * cell] = v;
+        out[2 * cell + 1] = 0.0f;
     }
 }
 
@@ -680,8 +651,7 @@ void coarse_deposit_cubes(const Geom& g, const int32_t* offsets, Planes p, float
     hipLaunchKernelGGL((k_coarse_deposit<BW, NT, L>), dim3(nb * nb * nb), dim3(NT), 0, s, g, offsets, p, mesh, scale);
 }
 
-void launch_coarse_deposit(const Geom& g, const int32_t* offsets, Planes p, float2* mesh, int32_t* /*overflow*/,
-                           hipStream_t s) {
+void launch_coarse_deposit(const Geom& g, const int32_t* offsets, Planes p, float2* mesh, hipStream_t s) {
     // acc in units of 2^-27 particle; density = mass / H^3 with H = r / f
     const double scale = std::ldexp(1.0, -27) * ((double)g.f * g.f * g.f) / ((double)g.r * g.r * g.r);
     // Cubes of 16 cells re-read least (1.42x), but a small mesh has too few of
@@ -749,13 +719,13 @@ void launch_fine_deposit(const Geom& g, const int32_t* offsets, Planes p, int ti
     if (g.periodic) {
         // the single periodic tile: 16^3 bricks over (16 / r + 2)^3 <= 6^3 source cells
         const int nb = (g.F + 15) / 16;
-        const dim3 grid(nb * nb * nb, ntiles), block(kDepThreads);
+        const dim3 grid(nb * nb * nb), block(kDepThreads);
         if (wide)
-            hipLaunchKernelGGL((k_deposit<16, DEP_FINE_PERIODIC, unsigned long long, 216, 2048>), grid, block, 0, s,
-                               g, offsets, p, mesh, g.F, g.r, log2D, scale, tile0);
+            hipLaunchKernelGGL((k_deposit<16, false, unsigned long long, 216, 2048>), grid, block, 0, s, g, offsets, p,
+                               mesh, g.F, g.r, log2D, scale);
         else
-            hipLaunchKernelGGL((k_deposit<16, DEP_FINE_PERIODIC, unsigned int, 216, 2048>), grid, block, 0, s, g,
-                               offsets, p, mesh, g.F, g.r, log2D, scale, tile0);
+            hipLaunchKernelGGL((k_deposit<16, false, unsigned int, 216, 2048>), grid, block, 0, s, g, offsets, p, mesh,
+                               g.F, g.r, log2D, scale);
         return;
     }
     // tile meshes: z-marching columns of 32 x 32 cells, a coarse layer per chunk
@@ -787,8 +757,8 @@ void diag_deposit(const Geom& g, const int32_t* offsets, Planes p, float2* mesh,
     const int H = g.r / g.f;                       // diagnostic cells per coarse cell
     const int nb = (g.ns + BW - 1) / BW;
     const int log2D = ilog2(512 / H);
-    hipLaunchKernelGGL((k_deposit<BW, DEP_DIAG, ACC, MAXSRC, MAPCAP>), dim3(nb * nb * nb), dim3(kDepThreads), 0, s, g,
-                       offsets, p, reinterpret_cast<float*>(mesh), g.ns, H, log2D, std::ldexp(1.0, -3 * log2D), 0);
+    hipLaunchKernelGGL((k_deposit<BW, true, ACC, MAXSRC, MAPCAP>), dim3(nb * nb * nb), dim3(kDepThreads), 0, s, g,
+                       offsets, p, reinterpret_cast<float*>(mesh), g.ns, H, log2D, std::ldexp(1.0, -3 * log2D));
 }
 
 }  // namespace

@@ -166,8 +166,7 @@ void launch_vc_encode(const Geom& g, const int32_t* offsets, Planes p, const Vel
                       StepScalars* sc, double* partial, hipStream_t s, bool gated = false);
 
 // ---- deposit.hip --------------------------------------------------------
-void launch_coarse_deposit(const Geom& g, const int32_t* offsets, Planes p, float2* mesh,
-                           int32_t* overflow, hipStream_t s);
+void launch_coarse_deposit(const Geom& g, const int32_t* offsets, Planes p, float2* mesh, hipStream_t s);
 // real density meshes of tiles [tile0, tile0 + ntiles) into mesh + k F^3;
 // wide selects 64-bit accumulators (needed when fine_deposit_needs_wide)
 void launch_fine_deposit(const Geom& g, const int32_t* offsets, Planes p, int tile0, int ntiles,
