@@ -2,8 +2,8 @@
 
 * ``stats``: per-kernel call counts and mean durations from a
   ``rocprofv3 --kernel-trace --stats --output-format csv`` run.
-* ``traffic``: HBM bytes per dispatch of every step kernel from two
-  ``--pmc FETCH_SIZE`` / ``--pmc WRITE_SIZE`` runs, each counter scaled by what
+* ``traffic``: HBM bytes of one execution of every step stage (all of its
+  kernels together) from two ``--pmc FETCH_SIZE`` / ``--pmc WRITE_SIZE`` runs, each counter scaled by what
   it reads for a plain device copy of known size in the same run (the bench's
   ``--calibrate-copy`` step), so the numbers are bytes, not counter units.
 
@@ -27,19 +27,22 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 PROFILES = os.path.join(ROOT, "profiles")
 
-# step stage (cube_profile_read name) -> kernel symbol fragment
-STAGE_KERNEL = {
-    "coarse_deposit": "k_coarse_deposit",
-    "coarse_fft_green": "k_fft<",
-    "fine_deposit": "k_deposit_zm<",
-    "fine_r2c_xy": "k_r2c_plane",
-    "fine_z_green": "k_zconv_half",
-    "fine_c2r_xy": "k_c2r_plane",
-    "gather_kick_drift": "k_gather<0,",
-    "scan_counts": "k_tile_scan",
-    "compact": "k_compact_brick",
-    "velocity_encode": "k_vc_encode",
-    "pp_force": "k_pp",
+# step stage (cube_profile_read name) -> patterns of the kernel that begins an
+# execution of it, of the kernels that may follow, and of one that must be among
+# them.  P(k) and the sort launch transforms and scans of their own, without
+# the kernel that must be there.
+STAGE_KERNELS = {
+    "coarse_deposit": (r"k_coarse_deposit", None, None),
+    "coarse_fft_green": (r"k_fft<\d+, 0, 0>|k_fft_xy<\d+, false, false>", r"k_fft<|k_fft_xy<", r"k_fft<\d+, 2, 2>"),
+    "fine_deposit": (r"k_deposit_zm<|k_deposit<\d+, false", None, None),
+    "fine_r2c_xy": (r"k_r2c_plane", None, None),
+    "fine_z_green": (r"k_zconv_half", None, None),
+    "fine_c2r_xy": (r"k_c2r_plane", None, None),
+    "gather_kick_drift": (r"k_gather<0,", None, None),
+    "scan_counts": (r"k_cell_stats", r"k_tile_sums|k_tile_scan|k_decide", r"k_tile_scan"),
+    "compact": (r"k_compact_brick", None, None),
+    "velocity_encode": (r"k_vc_mean", r"k_vc_sigma|k_vc_encode", r"k_vc_encode"),
+    "pp_force": (r"k_pp", None, None),
 }
 COPY_KERNELS = ("elementwise", "copyBuffer")
 
@@ -98,11 +101,24 @@ def _counter_rows(d, counter):
     return out
 
 
-def _means(rows):
-    acc = {}
-    for _, k, v in rows:
-        acc.setdefault(k, []).append(v)
-    return {k: sum(v) / len(v) for k, v in acc.items()}
+def stage_mean(rows, stage):
+    """Mean sum of the counter over the executions of a stage, or None without
+    one.  rows: (dispatch, kernel, value) of all dispatches of a run.  An
+    execution is a dispatch of the stage's first kernel and the dispatches of
+    its other kernels that follow it directly."""
+    first, others, must = (re.compile(p) if p else None for p in STAGE_KERNELS[stage])
+    runs, cur = [], None
+    for _, k, v in sorted(rows):
+        if first.match(k):
+            cur = [0.0, must is None]
+            runs.append(cur)
+        elif not (others and others.match(k)):
+            cur = None
+        if cur is not None:
+            cur[0] += v
+            cur[1] = cur[1] or bool(must.match(k))
+    sums = [v for v, whole in runs if whole]
+    return sum(sums) / len(sums) if sums else None
 
 
 def traffic_summary(fetch_dir, write_dir, copy_bytes, out_path, command):
@@ -122,24 +138,23 @@ def traffic_summary(fetch_dir, write_dir, copy_bytes, out_path, command):
     fv = [v for d, _, v in frows if d == did][0]
     f_scale = copy_bytes / (fv * 1024.0)
     w_scale = copy_bytes / (wv * 1024.0)
-    fetch, write = _means(frows), _means(wrows)
-    lines = ["# HBM traffic per dispatch from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (KiB per dispatch),",
+    lines = ["# HBM traffic of one execution of each stage from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (KiB),",
              f"# scaled by a {copy_bytes} B device copy in the same runs: read x{f_scale:.4f}, write x{w_scale:.4f}",
              f"# command: {command}", f"# source digest: {source_digest()}",
-             f"{'kernel':40s} {'read_MB':>10s} {'write_MB':>10s} {'traffic_MB':>11s}"]
-    for stage, frag in STAGE_KERNEL.items():
-        ks = [k for k in fetch if frag in k]
-        if not ks:
+             f"{'stage':40s} {'read_MB':>10s} {'write_MB':>10s} {'traffic_MB':>11s}"]
+    for stage in STAGE_KERNELS:
+        rd, wr = stage_mean(frows, stage), stage_mean(wrows, stage)
+        if rd is None or wr is None:
             continue
-        rd = sum(fetch[k] for k in ks) / len(ks) * 1024.0 * f_scale
-        wr = sum(write.get(k, 0.0) for k in ks) / len(ks) * 1024.0 * w_scale
+        rd *= 1024.0 * f_scale
+        wr *= 1024.0 * w_scale
         lines.append(f"{stage:40s} {rd / 1e6:10.3f} {wr / 1e6:10.3f} {(rd + wr) / 1e6:11.3f}")
     with open(out_path, "w") as f:
         f.write("\n".join(lines) + "\n")
 
 
 def lookup_traffic(stage, workload):
-    """Traffic (bytes per launch) of a stage from profiles/, or None when the
+    """Traffic (bytes per execution) of a stage from profiles/, or None when the
     summary is missing or was taken on different kernel sources."""
     path = os.path.join(PROFILES, f"traffic_{workload}.txt")
     if not os.path.exists(path):
