@@ -24,6 +24,7 @@
 #include <vector>
 
 #include "ctx.h"
+#include "hostutil.h"
 
 using namespace cube;
 
@@ -488,7 +489,7 @@ cube_status finish_general(cube_ctx* c, const StepPlan& next, void* scratch) {
     if (g.vcodec)
         for (int k = 0; k < 3; ++k) src.u[k] = dst.u[k] = nullptr;
     launch_general_keys(g, c->offsets, c->dir, c->far_key, key, s);
-    stable_sort_pairs(key, idx, kt, it, g.n, ilog2((int)std::min<int64_t>(g.ncells, 1 << 30)) + 1, true, ws, s);
+    stable_sort_pairs(key, idx, kt, it, g.n, key_bits(g.ncells), true, ws, s);
     launch_permute_planes(idx, src, dst, g.n, s);
     if (g.vcodec) launch_vc_encode(g, c->offsets_new, c->A, c->vcell, c->sc, c->partial, s, true);
     launch_step_commit(g, c->sc, c->counts_new, c->offsets_new, c->counts, c->offsets, next.wide, next.fmt == 2, s);
@@ -772,9 +773,7 @@ cube_status cube_compress(cube_ctx* c, const float* pos, const float* vel, int64
         return fail(CUBE_OOM, "compress: workspace allocation failed");
     launch_encode_keys(g, dpos, dvel, key, qp, vmax, n, s);
     launch_compress_scalars(c->sc, vmax, c->desc.v_headroom, s);
-    int bits = ilog2((int)std::min<int64_t>(g.ncells, (int64_t)1 << 30));
-    if (((int64_t)1 << bits) < g.ncells) ++bits;
-    stable_sort_pairs(key, idx, kt, it, n, bits, true, ws, s);
+    stable_sort_pairs(key, idx, kt, it, n, key_bits(g.ncells), true, ws, s);
     launch_key_offsets(key, n, g.ncells, c->counts, c->offsets, &c->sc->max_count, s);
     launch_cell_stats(g, c->counts, &c->sc->max_block8, s);
     launch_scatter_compressed(idx, qp, dvel, c->A, c->sc, n, s);
