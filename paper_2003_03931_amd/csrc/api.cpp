@@ -876,46 +876,36 @@ cube_status cube_forces(cube_ctx* c, float* acc, int32_t on_device) {
 
 namespace {
 
-// Copies that follow each other on both sides go as one (a view's planes are
-// mostly rows of one array, and so are the context's): a copy costs 2 to 4 us
-// whatever its size, and a state has seven arrays.
-struct CopyRuns {
-    hipStream_t stream;
-    hipMemcpyKind kind;
-    struct Part {
-        char* dst;
-        const char* src;
-        size_t bytes;
-    } part[12];
-    int parts = 0;
-
-    hipError_t copy(const Part& p, size_t bytes) { return hipMemcpyAsync(p.dst, p.src, bytes, kind, stream); }
-    hipError_t flush() {
-        size_t bytes = 0;
-        for (int i = 0; i < parts; ++i) bytes += part[i].bytes;
-        const int n = parts;
-        parts = 0;
-        if (n == 0 || copy(part[0], bytes) == hipSuccess) return hipSuccess;
-        // neighbours by chance: separate allocations are copied one by one
+// [p, p + bytes) is one device allocation's
+bool one_device_range(const void* p, size_t bytes) {
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) != hipSuccess) {
         (void)hipGetLastError();
-        for (int i = 0; i < n; ++i) {
-            const hipError_t e = copy(part[i], part[i].bytes);
-            if (e != hipSuccess) return e;
-        }
-        return hipSuccess;
+        return false;
     }
-    hipError_t add(void* d, const void* s, size_t n) {
-        if (parts) {
-            const Part& last = part[parts - 1];
-            if (d != last.dst + last.bytes || s != last.src + last.bytes) {
-                const hipError_t e = flush();
-                if (e != hipSuccess) return e;
-            }
-        }
-        part[parts++] = {static_cast<char*>(d), static_cast<const char*>(s), n};
-        return hipSuccess;
+    return static_cast<const char*>(p) + bytes <= static_cast<const char*>(base) + size;
+}
+
+// [p, p + bytes) is pageable at both ends: no allocation of the runtime
+bool pageable_range(const void* p, size_t bytes) {
+    for (const void* q : {p, static_cast<const void*>(static_cast<const char*>(p) + bytes - 1)}) {
+        hipPointerAttribute_t a{};
+        if (hipPointerGetAttributes(&a, q) != hipSuccess) (void)hipGetLastError();      // not the runtime's
+        else if (a.type != hipMemoryTypeUnregistered) return false;
     }
-};
+    return true;
+}
+
+// The copies of a state between a view and the context, in runs.
+auto state_copies(hipStream_t stream, hipMemcpyKind kind) {
+    const auto copy = [=](void* d, const void* s, size_t n) { return hipMemcpyAsync(d, s, n, kind, stream); };
+    const auto one = [=](const void* d, const void* s, size_t n) {
+        return (kind == hipMemcpyDeviceToHost ? pageable_range(d, n) : one_device_range(d, n)) &&
+               (kind == hipMemcpyHostToDevice ? pageable_range(s, n) : one_device_range(s, n));
+    };
+    return CopyRuns<decltype(copy), decltype(one)>(copy, one);
+}
 
 }  // namespace
 
@@ -926,7 +916,7 @@ cube_status cube_get_state(cube_ctx* c, cube_state_view* v) {
     if (!v || v->n_particles != g.n || v->n_cells != g.ncells) return fail(CUBE_INVALID, "state view size mismatch");
     hipStream_t s = c->stream;
     const hipMemcpyKind kind = v->on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-    CopyRuns copy{s, kind, {}, 0};
+    auto copy = state_copies(s, kind);
     for (int k = 0; k < 3; ++k)
         if (v->m[k]) CUBE_HIP(copy.add(v->m[k], c->A.m[k], g.n));
     for (int k = 0; k < 3; ++k)
@@ -959,7 +949,7 @@ cube_status cube_set_state(cube_ctx* c, const cube_state_view* v) {
     }
     hipStream_t s = c->stream;
     const hipMemcpyKind kind = v->on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
-    CopyRuns copy{s, kind, {}, 0};
+    auto copy = state_copies(s, kind);
     for (int k = 0; k < 3; ++k) CUBE_HIP(copy.add(c->A.m[k], v->m[k], g.n));
     for (int k = 0; k < 3; ++k) CUBE_HIP(copy.add(c->A.u[k], v->u[k], g.n));
     CUBE_HIP(copy.add(c->counts, v->counts, g.ncells * sizeof(int32_t)));
