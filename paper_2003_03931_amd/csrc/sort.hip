@@ -88,11 +88,12 @@ __global__ __launch_bounds__(kSortThreads) void k_digit_scatter(
             same &= (d >> b) & 1 ? m : ~m;
         }
         const int before = __popcll(same & lt);
-        rank[it] = 0;
-        if (ok) {
-            rank[it] = wc[wid][d] + before;
-            if (before == 0) wc[wid][d] += __popcll(same);
-        }
+        // every lane reads the count so far before the first of its digit raises it
+        const int so_far = wc[wid][d];
+        rank[it] = so_far + before;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (ok && before == 0) wc[wid][d] = so_far + __popcll(same);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
     }
