@@ -798,7 +798,7 @@ cube_status cube_decompress(cube_ctx* c, float* pos, float* vel, int64_t n, int3
     const size_t fb = (size_t)n * 3 * sizeof(float);
     Temp tmp(c->mem);
     if (!on_device && (!tmp.get(&dp, fb) || !tmp.get(&dv, fb))) return fail(CUBE_OOM, "decompress staging");
-    launch_decode(g, c->offsets, c->A, c->sc, c->vcell, dp, dv, s);
+    launch_decode(g, c->offsets, c->A, c->sc, c->vcell, dp, dv, c->max_count, s);
     if (!on_device) {
         hipMemcpyAsync(pos, dp, fb, hipMemcpyDeviceToHost, s);
         hipMemcpyAsync(vel, dv, fb, hipMemcpyDeviceToHost, s);

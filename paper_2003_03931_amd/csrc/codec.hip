@@ -117,7 +117,7 @@ __device__ __forceinline__ int lower_bound(const uint32_t* __restrict__ key, int
 // the keys to its cells' range with 256 probes a round, then finds where they
 // change: all of the range's keys are read, or, in a range longer than
 // kWalkKeys, each cell's first key is searched.  (Counting 11.2 million keys
-// one by one took 396 us of atomics, this takes 30.)
+// one by one took 396 us of atomics, this takes 43 to 49.)
 constexpr int kWalkKeys = 1 << 14;
 
 __global__ __launch_bounds__(256) void k_key_offsets(const uint32_t* __restrict__ key, int64_t n, int64_t ncells,
@@ -248,22 +248,35 @@ __global__ __launch_bounds__(256) void k_scatter_compressed(const uint32_t* __re
     }
 }
 
-// A workgroup decodes the particles of kDecodeCells consecutive cells, four
-// consecutive ones per thread (whole 4-byte loads of the planes, float4
+// A workgroup decodes the particles of up to kDecodeCells consecutive cells,
+// four consecutive ones per thread (whole 4-byte loads of the planes, float4
 // stores of the rows where the caller's arrays allow them; at the ends of the
 // range, which may split such a four, one at a time).  Store-bound: 24 bytes
 // out per particle for 6 in.  (A particle per thread, a row of cells per
-// workgroup: 176 us for 11.2 million; this: 90.)
+// workgroup: 176 us for 11.2 million; this: 92.)  The launch sizes the groups
+// for one round of 1024 particles.  In a concentrated state the few groups that
+// hold the particles need many rounds and are too few to hide their latency, so
+// four rounds' loads are issued together (2.1 million particles in 1/64 of the
+// cells, 64 a cell on average: 402 us round by round, 69 so), and the launch may
+// share a group among `gridDim.y` workgroups.
 constexpr int kDecodeCells = 128;
+constexpr int kDecodeRound = 4 * 256;        // particles
+constexpr int kDecodeSet = 4;                // rounds loaded together
 
 template <bool VEC>
-__global__ __launch_bounds__(256) void k_decode(Geom g, const int32_t* __restrict__ offsets, Planes in,
+__global__ __launch_bounds__(256) void k_decode(Geom g, const int32_t* __restrict__ offsets, int cells, Planes in,
                                                 const StepScalars* __restrict__ sc, VelCells vcell,
                                                 float* __restrict__ pos, float* __restrict__ vel) {
     __shared__ int offs[kDecodeCells + 1];
     __shared__ int cell[3][kDecodeCells];
-    const int64_t c0 = (int64_t)blockIdx.x * kDecodeCells;
-    const int nc = (int)min((int64_t)kDecodeCells, g.ncells - c0);
+    const int64_t c0 = (int64_t)blockIdx.x * cells;
+    const int nc = (int)min((int64_t)cells, g.ncells - c0);
+    const int lo = offsets[c0], hi = offsets[c0 + nc];
+    // this workgroup's part of the fours that hold [lo, hi), whole rounds
+    const int all4 = (hi + 3) / 4 - lo / 4, parts = (int)gridDim.y;
+    const int part4 = (all4 + 256 * parts - 1) / (256 * parts) * 256;
+    const int first4 = lo / 4 + (int)blockIdx.y * part4, end4 = min((hi + 3) / 4, first4 + part4);
+    if (first4 >= end4) return;
     for (int j = threadIdx.x; j <= nc; j += 256) offs[j] = offsets[c0 + j];
     if ((int)threadIdx.x < nc) {
         const int64_t c = c0 + threadIdx.x, tc3 = (int64_t)g.Tc * g.Tc * g.Tc;
@@ -275,25 +288,37 @@ __global__ __launch_bounds__(256) void k_decode(Geom g, const int32_t* __restric
     __syncthreads();
     const float H256 = (float)g.r / (float)(256 * g.f);   // H / 256, a power of two
     const double s = sc->s;
-    const int lo = offs[0], hi = offs[nc];
-    for (int p4 = lo / 4 + (int)threadIdx.x; 4 * (int64_t)p4 < hi; p4 += 256) {
-        const int p = 4 * p4;
+    struct Four {
         uint32_t m[3], u[3];
+    };
+    auto load = [&](int p4) {
+        Four f;
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            m[k] = reinterpret_cast<const uint32_t*>(in.m[k])[p4];
-            u[k] = reinterpret_cast<const uint32_t*>(in.u[k])[p4];
+            f.m[k] = reinterpret_cast<const uint32_t*>(in.m[k])[p4];
+            f.u[k] = reinterpret_cast<const uint32_t*>(in.u[k])[p4];
         }
+        return f;
+    };
+    auto put = [&](int p4, const Four& f) {
+        const int p = 4 * p4;
         int j = find_cell_fixed<7>(offs, nc, max(p, lo));
+        int next = offs[j + 1], at[3];           // the cell's end and coordinates
+#pragma unroll
+        for (int k = 0; k < 3; ++k) at[k] = cell[k][j] * 256;
         float x[12], v[12];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            while (j + 1 < nc && offs[j + 1] <= p + e) ++j;
+            if (next <= p + e && j + 1 < nc) {
+                do next = offs[++j + 1]; while (next <= p + e && j + 1 < nc);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) at[k] = cell[k][j] * 256;
+            }
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
-                const int q = cell[k][j] * 256 + (int)((m[k] >> (8 * e)) & 255u);
+                const int q = at[k] + (int)((f.m[k] >> (8 * e)) & 255u);
                 x[3 * e + k] = ((float)q + 0.5f) * H256;
-                const int c = (int)(int8_t)(u[k] >> (8 * e));
+                const int c = (int)(int8_t)(f.u[k] >> (8 * e));
                 v[3 * e + k] = g.vcodec ? (float)vc_decode(vcell.vc[k][c0 + j], s, vcell.tab, c) : (float)c * (float)s;
             }
         }
@@ -323,7 +348,18 @@ __global__ __launch_bounds__(256) void k_decode(Geom g, const int32_t* __restric
                         vel[3 * ((int64_t)p + e) + k] = v[3 * e + k];
                     }
         }
+    };
+    int p4 = first4 + (int)threadIdx.x;
+    // whole sets of rounds, every load within the range
+    constexpr int step = kDecodeSet * 256;
+    for (int at = first4; at + step <= end4; at += step, p4 += step) {
+        Four f[kDecodeSet];
+#pragma unroll
+        for (int u = 0; u < kDecodeSet; ++u) f[u] = load(p4 + 256 * u);
+#pragma unroll
+        for (int u = 0; u < kDecodeSet; ++u) put(p4 + 256 * u, f[u]);
     }
+    for (; p4 < end4; p4 += 256) put(p4, load(p4));
 }
 
 bool aligned16(const void* a, const void* b) {
@@ -359,12 +395,25 @@ void launch_scatter_compressed(const uint32_t* perm, const uint32_t* qpack, cons
 }
 
 void launch_decode(const Geom& g, const int32_t* offsets, Planes in, const StepScalars* sc,
-                   const VelCells& vcell, float* pos, float* vel, hipStream_t s) {
-    const dim3 grid(grid1d(g.ncells, kDecodeCells)), block(256);
+                   const VelCells& vcell, float* pos, float* vel, int max_count, hipStream_t s) {
+    // As many cells as hold one round's particles on average (with 128 whatever
+    // they hold, 4096 cells of 64 particles took 39 us, 25 now), and few enough
+    // for eight workgroups per CU, but not below 16: a row of cells per
+    // workgroup was faster than 128 cells in boxes too small to fill the chip.
+    const int64_t round = std::max<int64_t>(1, kDecodeRound * g.ncells / g.n);
+    const int64_t fill = std::max<int64_t>(16, g.ncells / (8 * device_cus()));
+    const int cells = (int)std::min({round, fill, (int64_t)kDecodeCells});
+    // Few groups of which some may hold many rounds' particles: up to eight
+    // workgroups each (2.1 million particles in 1/64 of the cells, 8 a cell on
+    // average: 123 us undivided, 68 shared by eight).  In a large box the extra
+    // workgroups, mostly idle, would cost more than the longest group.
+    const unsigned groups = grid1d(g.ncells, cells);
+    const bool heavy = (int64_t)cells * max_count > 8 * kDecodeRound;
+    const dim3 grid(groups, heavy ? std::min(8u, std::max(1u, 16384 / groups)) : 1), block(256);
     if (aligned16(pos, vel))
-        hipLaunchKernelGGL(k_decode<true>, grid, block, 0, s, g, offsets, in, sc, vcell, pos, vel);
+        hipLaunchKernelGGL(k_decode<true>, grid, block, 0, s, g, offsets, cells, in, sc, vcell, pos, vel);
     else
-        hipLaunchKernelGGL(k_decode<false>, grid, block, 0, s, g, offsets, in, sc, vcell, pos, vel);
+        hipLaunchKernelGGL(k_decode<false>, grid, block, 0, s, g, offsets, cells, in, sc, vcell, pos, vel);
 }
 
 }  // namespace cube

@@ -152,8 +152,9 @@ void launch_key_offsets(const uint32_t* sorted_key, int64_t n, int64_t ncells, i
                         int32_t* max_out, hipStream_t s);
 void launch_scatter_compressed(const uint32_t* perm, const uint32_t* qpack, const float* vel, Planes out,
                                StepScalars* sc, int64_t n, hipStream_t s);
+// max_count: the state's largest cell count
 void launch_decode(const Geom& g, const int32_t* offsets, Planes in, const StepScalars* sc,
-                   const VelCells& vcell, float* pos, float* vel, hipStream_t s);
+                   const VelCells& vcell, float* pos, float* vel, int max_count, hipStream_t s);
 
 // ---- vcodec.hip ---------------------------------------------------------
 // Cell-mean velocity codec (Eq. (3), Eq. (4)) on the FP32 velocities p.v of
