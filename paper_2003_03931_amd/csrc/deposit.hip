@@ -34,10 +34,16 @@ constexpr int kDepThreads = 256;
 // MAXSRC bounds the source window, (BW / cpc + 2)^3 coarse cells; MAPCAP is
 // the number of window particles whose source cell is looked up from a
 // per-particle map (larger windows fall back to a binary search).
+// full > 0: large bricks (kDiagBrick cells a side) whose window holds more
+// than `full` particles only mark the small bricks (kDiagPart) in them, in the
+// imaginary part of each one's first cell; small bricks, in a launch that
+// follows, return where they find no mark.
+constexpr int kDiagBrick = 16, kDiagPart = 8;
+
 template <int BW, bool DIAG, class ACC, int MAXSRC, int MAPCAP>
 __global__ __launch_bounds__(kDepThreads) void k_deposit(Geom g, const int32_t* __restrict__ offsets, Planes p,
                                                           float* __restrict__ out, int M, int cpc, int log2D,
-                                                          double scale) {
+                                                          double scale, int full) {
     static_assert(MAXSRC <= 1024, "fixed-step search over the source window");
     __shared__ __align__(16) ACC acc[BW * BW * BW];
     __shared__ int s_start[MAXSRC];
@@ -56,6 +62,9 @@ __global__ __launch_bounds__(kDepThreads) void k_deposit(Geom g, const int32_t* 
     const int nsrc = nsa[0] * nsa[1] * nsa[2];
     // source frame origin (coarse cells): one cell before the block
     const int S0[3] = {T0[0] / cpc - 1, T0[1] / cpc - 1, T0[2] / cpc - 1};
+
+    auto cell_at = [&](int x, int y, int z) { return (int64_t)x + (int64_t)M * (y + (int64_t)M * z); };
+    if (DIAG && BW == kDiagPart && full > 0 && out[2 * cell_at(T0[0], T0[1], T0[2]) + 1] == 0.0f) return;
 
     static_assert(sizeof(acc) % sizeof(uint4) == 0, "accumulators are cleared 16 bytes at a time");
     for (int i = threadIdx.x; i < (int)(sizeof(acc) / sizeof(uint4)); i += kDepThreads)
@@ -82,6 +91,13 @@ __global__ __launch_bounds__(kDepThreads) void k_deposit(Geom g, const int32_t* 
     }
     int total;
     int base = block_exclusive_scan(run, s_scan, &total);
+    if (DIAG && BW == kDiagBrick && full > 0 && total > full) {
+        constexpr int K = kDiagBrick / kDiagPart;
+        const int t = threadIdx.x;
+        const int x = T0[0] + t % K * kDiagPart, y = T0[1] + t / K % K * kDiagPart, z = T0[2] + t / (K * K) * kDiagPart;
+        if (t < K * K * K && x < M && y < M && z < M) out[2 * cell_at(x, y, z) + 1] = 1.0f;
+        return;
+    }
     const bool mapped = total <= MAPCAP;
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
@@ -166,8 +182,7 @@ __global__ __launch_bounds__(kDepThreads) void k_deposit(Geom g, const int32_t* 
             v.y = (float)fma((double)a[1], scale, -1.0);
             v.z = (float)fma((double)a[2], scale, -1.0);
             v.w = (float)fma((double)a[3], scale, -1.0);
-            const int64_t cell = (int64_t)(T0[0] + ix) + (int64_t)M * ((T0[1] + iy) + (int64_t)M * (T0[2] + iz));
-            *reinterpret_cast<float4*>(out + cell) = v;
+            *reinterpret_cast<float4*>(out + cell_at(T0[0] + ix, T0[1] + iy, T0[2] + iz)) = v;
         }
         return;
     }
@@ -175,7 +190,7 @@ __global__ __launch_bounds__(kDepThreads) void k_deposit(Geom g, const int32_t* 
         const int ix = i % BW, iy = (i / BW) % BW, iz = i / (BW * BW);
         if (ix >= bw[0] || iy >= bw[1] || iz >= bw[2]) continue;
         const float v = (float)((double)acc[i] * scale - 1.0);
-        const int64_t cell = (int64_t)(T0[0] + ix) + (int64_t)M * ((T0[1] + iy) + (int64_t)M * (T0[2] + iz));
+        const int64_t cell = cell_at(T0[0] + ix, T0[1] + iy, T0[2] + iz);
         out[2 * cell] = v;
         out[2 * cell + 1] = 0.0f;
     }
@@ -722,10 +737,10 @@ void launch_fine_deposit(const Geom& g, const int32_t* offsets, Planes p, int ti
         const dim3 grid(nb * nb * nb), block(kDepThreads);
         if (wide)
             hipLaunchKernelGGL((k_deposit<16, false, unsigned long long, 216, 2048>), grid, block, 0, s, g, offsets, p,
-                               mesh, g.F, g.r, log2D, scale);
+                               mesh, g.F, g.r, log2D, scale, 0);
         else
             hipLaunchKernelGGL((k_deposit<16, false, unsigned int, 216, 2048>), grid, block, 0, s, g, offsets, p, mesh,
-                               g.F, g.r, log2D, scale);
+                               g.F, g.r, log2D, scale, 0);
         return;
     }
     // tile meshes: z-marching columns of 32 x 32 cells, a coarse layer per chunk
@@ -753,12 +768,38 @@ bool fp16_density_fits(const Geom& g, int max_block8) {
 namespace {
 
 template <int BW, class ACC, int MAXSRC, int MAPCAP>
-void diag_deposit(const Geom& g, const int32_t* offsets, Planes p, float2* mesh, hipStream_t s) {
+void diag_bricks(const Geom& g, const int32_t* offsets, Planes p, float2* mesh, int full, hipStream_t s) {
     const int H = g.r / g.f;                       // diagnostic cells per coarse cell
     const int nb = (g.ns + BW - 1) / BW;
     const int log2D = ilog2(512 / H);
     hipLaunchKernelGGL((k_deposit<BW, true, ACC, MAXSRC, MAPCAP>), dim3(nb * nb * nb), dim3(kDepThreads), 0, s, g,
-                       offsets, p, reinterpret_cast<float*>(mesh), g.ns, H, log2D, std::ldexp(1.0, -3 * log2D));
+                       offsets, p, reinterpret_cast<float*>(mesh), g.ns, H, log2D, std::ldexp(1.0, -3 * log2D), full);
+}
+
+// Bricks of 16 cells re-read less than bricks of 8 (1.95x against 3.4x at
+// H = 2, 3.4x against 8x at H = 4): 488 against 786 us for all of P(k) of 256^3
+// particles at H = 4.  But a mesh below 128 has fewer of them than twice the
+// CUs (64: 96 us against 65, 111 against 72 at H = 4), and where the particles
+// are concentrated the bricks that hold them are few (256^3 in 1/64 of the
+// volume: 3.8 ms against 2.9): a large brick whose window holds more than
+// three times the average, and more than 0.6 of a CU's share of all windows
+// (below that the others hide it), is left to small ones: 2.6 ms.  That second
+// launch is skipped where no window can be that full.
+template <class ACC, int SRC8, int MAP8, int SRC16, int MAP16>
+void diag_deposit(const Geom& g, const int32_t* offsets, Planes p, float2* mesh, int max_block8, hipStream_t s) {
+    const int H = g.r / g.f;
+    const int64_t nb = (g.ns + kDiagBrick - 1) / kDiagBrick, cus = device_cus();
+    if (nb * nb * nb < 2 * cus) {
+        diag_bricks<kDiagPart, ACC, SRC8, MAP8>(g, offsets, p, mesh, 0, s);
+        return;
+    }
+    const int64_t w = kDiagBrick / H + 2;          // window side; even, so blocks of 2 cells cover it
+    const double window = (double)(w * w * w) * g.n / g.ncells;
+    const double limit = std::max(3.0 * window, 0.6 * window * (double)(nb * nb * nb) / (double)cus);
+    const bool even = (double)max_block8 * (double)(w / 2 * (w / 2) * (w / 2)) <= limit;
+    const int full = even ? 0 : (int)std::min(limit, 2147483647.0);
+    diag_bricks<kDiagBrick, ACC, SRC16, MAP16>(g, offsets, p, mesh, full, s);
+    if (full) diag_bricks<kDiagPart, ACC, SRC8, MAP8>(g, offsets, p, mesh, full, s);
 }
 
 }  // namespace
@@ -767,21 +808,21 @@ void launch_diag_deposit(const Geom& g, const int32_t* offsets, Planes p, float2
                          hipStream_t s) {
     const int H = g.r / g.f;
     if (H == 1) {
-        diag_deposit<8, unsigned long long, 1000, 10240>(g, offsets, p, mesh, s);
+        diag_bricks<kDiagPart, unsigned long long, 1000, 10240>(g, offsets, p, mesh, 0, s);
         return;
     }
     // a cell is at most half a coarse cell wide and gathers the particles of
-    // at most one 2 x 2 x 2 block of coarse cells, as on the fine mesh.  Bricks
-    // of 16 re-read less than bricks of 8 (1.95x against 3.4x at H = 2, 3.4x
-    // against 8x at H = 4), and 32-bit accumulators take half of their LDS:
-    // 594 -> 278 us for 256^3 particles at H = 4.
+    // at most one 2 x 2 x 2 block of coarse cells, as on the fine mesh, so
+    // 32-bit accumulators are exact below the same kind of bound; they take
+    // half of the LDS (594 -> 278 us with bricks of 16 for 256^3 particles at
+    // H = 4)
     const bool wide = (double)max_block8 * std::ldexp(1.0, 27) / ((double)H * H * H) >= 4294967296.0;
     if (H == 2) {
-        if (wide) diag_deposit<16, unsigned long long, 1000, 8192>(g, offsets, p, mesh, s);
-        else diag_deposit<16, unsigned int, 1000, 8192>(g, offsets, p, mesh, s);
+        if (wide) diag_deposit<unsigned long long, 216, 8192, 1000, 8192>(g, offsets, p, mesh, max_block8, s);
+        else diag_deposit<unsigned int, 216, 8192, 1000, 8192>(g, offsets, p, mesh, max_block8, s);
     } else {
-        if (wide) diag_deposit<16, unsigned long long, 216, 4096>(g, offsets, p, mesh, s);
-        else diag_deposit<16, unsigned int, 216, 4096>(g, offsets, p, mesh, s);
+        if (wide) diag_deposit<unsigned long long, 64, 8192, 216, 4096>(g, offsets, p, mesh, max_block8, s);
+        else diag_deposit<unsigned int, 64, 8192, 216, 4096>(g, offsets, p, mesh, max_block8, s);
     }
 }
 
