@@ -224,15 +224,16 @@ __global__ __launch_bounds__(kDepThreads) void k_deposit(Geom g, const int32_t* 
 // With eight planes a layer (cpc = 8) that would leave one workgroup per CU:
 // there (TWO) a second phase takes and stores the planes just finished, from a
 // ring of CZ + 2, and issues the next chunk's loads before (500 us as one
-// phase of 1024 threads, 463 as two of 512).
+// phase of 1024 threads, 456 to 463 as two of 512; chunks of two phases in
+// whole columns took 464 to 475).
 // Source tables are built two chunks ahead: ranges loaded and counts scanned
 // within the waves in one phase, ranks finished in the next.
 //
 // A column may be cut in z: part i of `parts` finishes the planes of its own
 // chunks and starts one chunk early, whose particles reach its first planes.
 // The launch cuts where workgroups would leave the chip's last round empty
-// (column_parts).  64 tiles of a 1024^3 step: 470 us in two phases and whole
-// columns, 400 now (1.05 GB written, 2.9 TB/s in all); 8 tiles 111 -> 57.
+// (column_parts).  64 tiles of a 1024^3 step: 471 us in two phases and whole
+// columns, 415 now (1.27 GB moved, 3.1 TB/s); 8 tiles 111 -> 59.
 template <int BW, int CZ, int NT, int U, bool TWO, class ACC, int MAXSRC, int MAPCAP>
 __global__ __launch_bounds__(NT) void k_deposit_zm(Geom g, const int32_t* __restrict__ offsets, Planes p,
                                                     float* __restrict__ out, int cpc, int log2D, double scale,
@@ -509,10 +510,13 @@ __device__ __forceinline__ unsigned quad_xor(unsigned v) {
 // sums: the result does not depend on the order and equals the
 // particle-by-particle deposit bit for bit.
 //
-// Bound by vector instructions, about 60 per particle (HBM would take 1 ms of
-// a 1024^3 step's deposit).  A cell per thread with byte loads, bounds checks
-// per slot and a wave waiting at every cell for its fullest one took 9.06 ms
-// there, lanes stepping through their own cells take 5.68.
+// Bound by vector instructions: in the 1024^3 step 1.02 per clock and CU with
+// 42 of 64 lanes at work (cells of eight particles on average go by fours, and
+// a wave is as long as its longest lane), 146 lane slots for each particle and
+// cube that reads it (1.42 of them).  Its 7.8 GB would take 1.3 ms.  A cell per
+// thread with byte loads, bounds checks per slot and a wave waiting at every
+// cell for its fullest one took 9.06 ms there, lanes stepping through their own
+// cells take 5.7 to 6.1.
 template <int BW, int NT, int L>
 __global__ __launch_bounds__(NT) void k_coarse_deposit(Geom g, const int32_t* __restrict__ offsets, Planes p,
                                                         float2* __restrict__ out, double scale) {
@@ -691,8 +695,8 @@ namespace {
 // Parts that a column is cut in.  A part of n chunks takes about n + 2 phases
 // (its first chunk is another part's last, and the pipeline fills); the chip
 // holds `slots` workgroups at a time, and beyond one round of them the last
-// one is on average little more than half full.  With columns of 40 chunks on
-// 768 slots: 1600 columns (64 tiles of 160^3) 445, 404, 400, 406, 420 us in 1,
+// one is on average little more than half full.  Timed alone, with columns of
+// 40 chunks on 768 slots: 1600 columns (64 tiles of 160^3) 445, 404, 400, 406, 420 us in 1,
 // 2, 3, 4, 6 parts; 200 columns 98, 65, 57, 66, 60; 25 columns 86 us in one
 // part, 21 in 14.
 int column_parts(int64_t columns, int chunks, int slots) {

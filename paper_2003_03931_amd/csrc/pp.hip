@@ -37,13 +37,14 @@
 // a cell, three stages: 0.4 to 0.9.  With a whole cell's reach every lane needs
 // every row, and staging is faster at any number (0.87 at 600 a cell).
 //
-// Bound by instruction issue (0.99 vector instructions per clock and CU, half
-// of the lanes at work).  One particle in six of a neighbourhood is in reach,
+// Bound by instruction issue (1.19 vector instructions per clock and CU on
+// 1024^3 particles, 26 of 64 lanes at work).  One particle in six of a neighbourhood is in reach,
 // yet some lane of a wave is at almost every step, so a single loop computes
 // the weight at every step.  Here the loop over partners only measures
 // distances and lists the pairs in reach; the weights are computed from the
 // lists, in the order the pairs were met (96^3 particles, r_pp = 4 fine cells:
-// 240 us -> 207; with lists of 24 or 32 pairs 4 and 13 % more).
+// 240 us -> 207; with lists of 24 or 32 pairs 4 and 13 % more; 197 with the
+// staging loads in flight together).
 //
 // The accelerations go to three FP32 planes in canonical order, which the
 // gather adds to the mesh force before the kick.
